@@ -675,11 +675,32 @@ hipError_t launch_conv3d_dgrad(Vol v, int Cout, const __bf16* dY, const __bf16* 
   return launch_tiled_n(v, io, Cin, s);
 }
 
+// Bias gradient: partial sums in the start of a consumed weight workspace, then their sum.
+static hipError_t launch_bias(Vol v, int Cout, const __bf16* dY, const __bf16* Yact, int nsplit, int chunk,
+                              float* part, float* db, hipStream_t s) {
+  hipLaunchKernelGGL(k_bias_part, dim3(nsplit), dim3(64), 0, s, v, Cout, dY, Yact, chunk, part);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_reduce_splits, dim3(nblk(Cout)), dim3(256), 0, s, nsplit, (size_t)Cout, part, db);
+  return hipGetLastError();
+}
+
 hipError_t launch_conv3d_wgrad(Vol v, int C1, int C2, const __bf16* X1, const __bf16* X2, int Cout, const __bf16* dY,
                                const __bf16* Yact, int nsplit, float* part, float* dW, float* db, hipStream_t s) {
   size_t P = (size_t)v.D * v.H * v.W;
   int chunk = (int)((P + nsplit - 1) / nsplit);
   int Cin = C1 + C2;
+  const bool mfma = conv3d_wgrad_mfma_ok(X1, X2, Cout, dY, Yact);
+  if (mfma) {
+    const int ns = conv3d_wgrad_splits(Cin, nsplit);
+    if (ns > 0) return launch_conv3d_wgrad_mfma(v, C1, C2, X1, X2, Cout, dY, Yact, ns, part, dW, db, s);
+    hipError_t e = launch_conv3d_wgrad_mfma(v, C1, C2, X1, X2, Cout, dY, Yact, 1, part, dW, nullptr, s);
+    if (e != hipSuccess) return e;
+    // one split: the bias is summed over chunks of its own in the consumed workspace
+    nsplit = (int)(P / 512 + 1 < (size_t)27 * Cin ? P / 512 + 1 : (size_t)27 * Cin);
+    chunk = (int)((P + nsplit - 1) / nsplit);
+    return launch_bias(v, Cout, dY, Yact, nsplit, chunk, part, db, s);
+  }
   dim3 grid(27, nblk((size_t)Cout * Cin), nsplit);
   hipLaunchKernelGGL(k_conv3d_wgrad_part, grid, dim3(256), 0, s, v, C1, C2, X1, X2, Cout, dY, Yact, chunk, part);
   hipError_t e = hipGetLastError();
@@ -688,12 +709,7 @@ hipError_t launch_conv3d_wgrad(Vol v, int C1, int C2, const __bf16* X1, const __
   hipLaunchKernelGGL(k_reduce_splits, dim3(nblk(n)), dim3(256), 0, s, nsplit, n, part, dW);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // bias: reuse the start of the partial buffer (the weight partials are consumed)
-  hipLaunchKernelGGL(k_bias_part, dim3(nsplit), dim3(64), 0, s, v, Cout, dY, Yact, chunk, part);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_reduce_splits, dim3(nblk(Cout)), dim3(256), 0, s, nsplit, (size_t)Cout, part, db);
-  return hipGetLastError();
+  return launch_bias(v, Cout, dY, Yact, nsplit, chunk, part, db, s);
 }
 
 hipError_t launch_prep_weights(int Cout, int Cin, int Kpf, int Kpd, const float* W, __bf16* Wt, __bf16* Wd,
