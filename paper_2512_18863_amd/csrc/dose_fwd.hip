@@ -7,6 +7,8 @@
 //   conv          beam-frame dose Dfan = K_k (*) P_k         (§2.2.5-2.2.6, Eq. 8)
 //   k_gather      dose += MU_b trilinear(Dfan_b)             (§2.2.7, Eq. 9)
 // k_frame and k_transpose_rho prepare per-call constants.
+#include <type_traits>
+
 #include "taps.hpp"
 
 namespace pdrt {
@@ -634,89 +636,128 @@ hipError_t launch_conv_direct(const Geo<T>& g, int nb, const T* z, const T* in, 
 
 // ------------------------------------------------------------------ gather
 
-// Back-projection and MU-weighted sum (§2.2.7, Eq. 9).  One thread per voxel,
-// lanes along z so the 2 x 2 beam-frame columns a wavefront reads are contiguous
-// in v.  The sum over control points uses Neumaier compensation; across batches
-// the running sum lives in `dose` and its compensation in `comp`.
+// Back-projection and MU-weighted sum (§2.2.7, Eq. 9):
+// dose(x, y, z) += sum_b MU_b trilinear(Dfan_b at the voxel's beam-frame position).
 //
-// Workgroups are numbered so that each of the eight XCDs (which receive
-// workgroups round robin) walks a contiguous range of y slabs: neighbouring voxel
-// columns read the same beam-frame columns, and they then share one L2.
-// The part of one control point's trilinear lookup that depends only on the
-// voxel column (x, y): the beam-frame plane k and row i of the column (the same
-// for every z), the four (k, i) corner weights with their in-grid masks and the
-// corners' element offsets within the control point's beam-frame volume, and
-// SAD / d, which scales z into the lateral coordinate j.
+// A voxel column (x, y) meets one beam-frame cell (k, i) per control point, the same
+// for all its z, so the lookup separates: the column's four rows (k, i), (k, i + 1),
+// (k + 1, i), (k + 1, i + 1) are first blended into one row over j, which its z then
+// read at j0 and j0 + 1.  One wavefront owns a column and ZS z per lane (lanes along
+// z): its lanes load the four rows coalesced (lanes along j), blend them with the
+// corner weights (times MU) and park the blended row in LDS; every z then takes two
+// neighbouring words of it.  A control point whose fan misses the column is skipped.
+// Against eight loads and eight weighted adds per voxel and control point this is 4
+// Nv / nz of each, and reads whole cache lines.  180 control points at 128^3 (89-wide
+// planes, 1.04 GB of Dfan): 0.41 ms (2.6 TB/s; eight loads per voxel: 0.92 ms); 90 at
+// 128 x 128 x 96 (43-wide): 0.084 ms (0.33).  Latency of the loads bounds it.
+//
+// The terms are summed in control-point order, in FP64 for the FP32 path (an exact
+// sum of FP32 terms to 53 bits, two instructions a term where the compensated FP32
+// sum takes seven) and with Neumaier compensation for the FP64 path; across batches
+// the running sum lives in `dose` and `comp`.
+//
+// A block's four wavefronts cover a 2 x 2 patch of columns: neighbouring columns read
+// mostly the same beam-frame rows.  Workgroups are numbered so that each of the
+// eight XCDs (which receive workgroups round robin) walks a contiguous range of
+// patches and they share one L2.
+
+// One control point's terms of a voxel column, its fan reaching the column.
 template <typename T>
 struct GatherCol {
-  T q;
-  T w[4];     // corner (dk, di) = (c >> 1, c & 1): in-grid mask x (1 - wk or wk) x (1 - wi or wi)
-  int off[4]; // element offset of the corner's row (clamped into the grid)
+  T w[4];      // corner (dk, di) = (c >> 1, c & 1): MU x in-grid mask x (1 - wk or wk) x (1 - wi or wi)
+  int off[4];  // element offset of the corner's row (clamped into the grid)
+  T q;         // SAD / d, which scales z into the lateral coordinate j
+  int b;       // control point within the batch
 };
 
-constexpr int GATHER_CHUNK = 64;  // control points whose column terms sit in LDS at once
+constexpr int GATHER_CHUNK = 64;  // control points examined at once, one per lane
+constexpr int GATHER_PAD = 2;     // zero words on each side of a blended row
 
-// A wavefront-uniform value read from LDS, moved to scalar registers (so that
-// addresses built from it use the scalar base of a global load).
+// A wavefront-uniform value moved to a scalar register (so that addresses built from
+// it use the scalar base of a global load).
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ float uniform(float v) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
-__device__ __forceinline__ double uniform(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffLL)), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
 
-// dose(x, y, z) += sum_b MU_b trilinear(Dfan_b at the voxel's beam-frame position).
-// A block covers 64 consecutive z of a 4 x 4 patch of voxel columns (one
-// wavefront per column).  The beam-frame rows that a column reads are shared with
-// its neighbours in x and y, so a square patch reads about (4 + 1)^2 distinct rows
-// per control point for 16 columns, where a line of four columns reads about
-// 2 (4 + 1) for 4 (blocks drift apart over the control points, so rows shared
-// between blocks come from beyond L2 again).  The column terms of each control
-// point are computed once per block (into LDS) instead of once per voxel, and each
-// lane does only the z-dependent part: the lateral coordinate j, the eight loads
-// and the interpolation (the four (k, i) corners weighted first, in columns j and
-// j + 1, then the step along j).  The terms are summed in control-point order with
-// a compensated sum.
-constexpr int GATHER_P = 4;                  // patch edge (voxel columns)
-constexpr int GATHER_NW = GATHER_P * GATHER_P;  // wavefronts per block
-
+// Running sum over control points.
 template <typename T>
-__global__ void __launch_bounds__(64 * GATHER_NW) k_gather(Geo<T> g, int nb, int first, int last, int zc, int xc,
-                                                           int yc, const T* __restrict__ frame,
-                                                           const T* __restrict__ mu, const T* __restrict__ Dfan,
-                                                           T* __restrict__ dose, T* __restrict__ comp) {
-  constexpr int NT = 64 * GATHER_NW;
-  __shared__ GatherCol<T> cols[GATHER_NW][GATHER_CHUNK];
+struct GatherSum;
+
+template <>
+struct GatherSum<float> {
+  double s = 0.0;
+  __device__ void add(float v) { s += (double)v; }
+  // the sum's 64 bits, split over two words, carried between batches
+  __device__ void load(float a, float c) {
+    s = __hiloint2double(__float_as_int(a), __float_as_int(c));
+  }
+  __device__ void store(float* a, float* c) const {
+    *a = __int_as_float(__double2hiint(s));
+    *c = __int_as_float(__double2loint(s));
+  }
+  __device__ float value(float calib) const { return calib * (float)s; }
+};
+
+template <>
+struct GatherSum<double> {
+  double s = 0.0, c = 0.0;
+  __device__ void add(double v) {
+    const double t = s + v;
+    c += fabs(s) >= fabs(v) ? (s - t) + v : (v - t) + s;
+    s = t;
+  }
+  __device__ void load(double a, double b) { s = a, c = b; }
+  __device__ void store(double* a, double* b) const { *a = s, *b = c; }
+  __device__ double value(double calib) const { return calib * (s + c); }
+};
+
+// JS: ceil(Nv / 64), or 0 for a loop over wider planes; ZS: z per lane; PX x PY: the
+// block's patch of columns; U: control points in flight.
+template <typename T, int JS, int ZS, int PX, int PY, int U>
+__global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int first, int last, int zc, int xc, int yc,
+                                                         const T* __restrict__ frame, const T* __restrict__ mu,
+                                                         const T* __restrict__ Dfan, T* __restrict__ dose,
+                                                         T* __restrict__ comp) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr int NW = PX * PY;
   const int nblk = zc * xc * yc;
   const int per_xcd = (nblk + 7) / 8;
   const int w = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (w >= nblk) return;  // uniform over the block
+  if (w >= nblk) return;
   const int zq = w % zc, xq = (w / zc) % xc, yq = w / (zc * xc);
-  const int wave = threadIdx.x >> 6;
-  const int z = zq * 64 + (threadIdx.x & 63);
-  const int x = xq * GATHER_P + wave % GATHER_P;
-  const int y = yq * GATHER_P + wave / GATHER_P;
-  const bool active = z < g.nz && x < g.nx && y < g.ny;
-  const size_t vox = ((size_t)z * g.ny + y) * g.nx + x;
-  const T tz = g.rel_oz + T(z) * g.sz;
-  T s = T(0), c = T(0);
-  if (active && !first) {
-    s = dose[vox];
-    c = comp[vox];
+  const int lane = threadIdx.x & 63;
+  const int wave = uniform(threadIdx.x >> 6);
+  const int x = xq * PX + wave % PX, y = yq * PY + wave / PX;
+  if (x >= g.nx || y >= g.ny) return;  // (wavefronts are independent: no barriers below)
+  const int z0 = zq * 64 * ZS + lane;
+  const int js = JS ? JS : (g.Nv + 63) / 64;
+  const int pitch = 64 * js + 2 * GATHER_PAD;
+  GatherCol<T>* cols = reinterpret_cast<GatherCol<T>*>(smem_raw) + wave * GATHER_CHUNK;
+  T* rows = reinterpret_cast<T*>(smem_raw + NW * GATHER_CHUNK * sizeof(GatherCol<T>)) + (size_t)wave * U * pitch;
+  for (int q = lane; q < U * pitch; q += 64) rows[q] = T(0);  // the words beside j = 0 .. Nv - 1 stay zero
+
+  GatherSum<T> sum[ZS];
+  T tz[ZS];
+#pragma unroll
+  for (int s = 0; s < ZS; ++s) {
+    const int z = z0 + 64 * s;
+    tz[s] = (g.rel_oz + T(z) * g.sz) * g.inv_lat;
+    if (!first && z < g.nz) {
+      const size_t vox = ((size_t)z * g.ny + y) * g.nx + x;
+      sum[s].load(dose[vox], comp[vox]);
+    }
   }
   const int plane = g.Nu * g.Nv;
   const size_t cp_elems = (size_t)g.Nk * plane;
+  const T tx = g.rel_ox + T(x) * g.sx, ty = g.rel_oy + T(y) * g.sy;
+  bool bad = false;  // a non-finite MU makes every voxel NaN, also those its fan misses
   for (int b0 = 0; b0 < nb; b0 += GATHER_CHUNK) {
-    const int nbc = min(GATHER_CHUNK, nb - b0);
-    __syncthreads();  // the previous chunk's column terms are no longer read
-    for (int e = threadIdx.x; e < GATHER_NW * nbc; e += NT) {
-      const int cw = e / nbc, bb = e - cw * nbc, b = b0 + bb;
-      const T tx = g.rel_ox + T(xq * GATHER_P + cw % GATHER_P) * g.sx;
-      const T ty = g.rel_oy + T(yq * GATHER_P + cw / GATHER_P) * g.sy;
-      const T sn = frame[2 * b], cs = frame[2 * b + 1];
+    // this lane's control point: its cell (k, i) and weights; those that reach the
+    // column are listed in control-point order
+    const int b = b0 + lane;
+    bool hit = false;
+    GatherCol<T> col;
+    if (b < nb) {
+      const T sn = frame[2 * b], cs = frame[2 * b + 1], m = mu[b];
+      bad |= !(m - m == T(0));
       // voxel_to_fan without the z part
       const T ev = -sn * tx + cs * ty;
       const T q = T(1) / (T(1) + ev * g.inv_sad);
@@ -724,104 +765,142 @@ __global__ void __launch_bounds__(64 * GATHER_NW) k_gather(Geo<T> g, int nb, int
       const T fkv = (ev - g.e0) * g.inv_dstep, fiv = u * g.inv_lat + g.cu;
       const T fk = dfloor(fkv), fi = dfloor(fiv);
       const bool in_ki = (fk >= T(-1)) & (fk < T(g.Nk)) & (fi >= T(-1)) & (fi < T(g.Nu));
+      hit = !((fk < T(-1)) | (fk >= T(g.Nk)) | (fi < T(-1)) | (fi >= T(g.Nu)));  // (a NaN angle is not skipped)
       const int k0 = in_ki ? (int)fk : 0, i0 = in_ki ? (int)fi : 0;
       const T wk = fkv - fk, wi = fiv - fi;
-      GatherCol<T> col;
       col.q = q;
+      col.b = b;
 #pragma unroll
       for (int dk = 0; dk < 2; ++dk)
 #pragma unroll
         for (int di = 0; di < 2; ++di) {
           const int kk = k0 + dk, ii = i0 + di;
-          const bool ok = in_ki & (kk >= 0) & (kk < g.Nk) & (ii >= 0) & (ii < g.Nu);
+          const bool ok = (kk >= 0) & (kk < g.Nk) & (ii >= 0) & (ii < g.Nu);
           const T wkk = dk ? wk : T(1) - wk, wii = di ? wi : T(1) - wi;
-          col.w[2 * dk + di] = T(ok) * (wkk * wii);
+          col.w[2 * dk + di] = ok ? m * (wkk * wii) : T(0);
           col.off[2 * dk + di] = min(max(kk, 0), g.Nk - 1) * plane + min(max(ii, 0), g.Nu - 1) * g.Nv;
         }
-      cols[cw][bb] = col;
     }
-    __syncthreads();
-    if (active) {
-      // the eight loads of a control point, then its term (in control-point order);
-      // groups of four control points keep 32 loads in flight
-      struct Term {
-        T lo[4], hi[4], wj, jin0, jin1, in_j;
-      };
-      auto fetch = [&](int bb, Term& tm) {
-        const GatherCol<T>& col = cols[wave][bb];
-        const T q = uniform(col.q);
-        const T fjv = tz * q * g.inv_lat + g.cv;
-        const T fj = dfloor(fjv);
-        const bool in_j = (fj >= T(-1)) & (fj < T(g.Nv));
-        const int j0 = in_j ? (int)fj : 0;
-        tm.wj = fjv - fj;
-        tm.in_j = T(in_j);
-        const int ja = max(j0, 0), jb = min(j0 + 1, g.Nv - 1);
-        tm.jin0 = T(j0 >= 0);
-        tm.jin1 = T(j0 + 1 < g.Nv);
-        const T* base = Dfan + (size_t)(b0 + bb) * cp_elems;
-        // 32-bit unsigned byte offsets from a scalar row address (the load's scalar base)
-        const unsigned oa = (unsigned)ja * (unsigned)sizeof(T), ob = (unsigned)jb * (unsigned)sizeof(T);
+    const unsigned long long mask = __ballot(hit);
+    if (hit) cols[__popcll(mask & ((1ull << lane) - 1ull))] = col;
+    const int n = __popcll(mask);
+    __builtin_amdgcn_wave_barrier();
+
+    // UU listed control points: all their row loads, then the blended rows, then the z
+    auto take = [&](int e0, auto uu) {
+      constexpr int UU = decltype(uu)::value;
+      if constexpr (JS > 0) {
+        T v[UU][JS][4];
 #pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-          const char* row = reinterpret_cast<const char*>(base + uniform(col.off[cc]));
-          tm.lo[cc] = *reinterpret_cast<const T*>(row + oa);
-          tm.hi[cc] = *reinterpret_cast<const T*>(row + ob);
+        for (int u = 0; u < UU; ++u) {
+          const GatherCol<T>& c = cols[e0 + u];
+          const T* base = Dfan + (size_t)uniform(c.b) * cp_elems;
+#pragma unroll
+          for (int cc = 0; cc < 4; ++cc) {
+            const T* row = base + uniform(c.off[cc]);
+#pragma unroll
+            for (int s = 0; s < JS; ++s) v[u][s][cc] = row[(unsigned)min(64 * s + lane, g.Nv - 1)];
+          }
         }
-      };
-      auto add = [&](int bb, const Term& tm) {
-        const GatherCol<T>& col = cols[wave][bb];
-        // the (k, i) corners weighted first (columns j and j + 1), then the j step
-        T lo = T(0), hi = T(0);
 #pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-          const T w = uniform(col.w[cc]);
-          lo += w * tm.lo[cc];
-          hi += w * tm.hi[cc];
+        for (int u = 0; u < UU; ++u) {
+          const GatherCol<T>& c = cols[e0 + u];
+#pragma unroll
+          for (int s = 0; s < JS; ++s) {
+            T r = T(0);
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc) r += c.w[cc] * v[u][s][cc];
+            if (64 * s + lane < g.Nv) rows[u * pitch + GATHER_PAD + 64 * s + lane] = r;
+          }
         }
-        const T a = tm.jin0 * lo, bv = tm.jin1 * hi;
-        const T acc = a + tm.wj * (bv - a);
-        // outside the beam-frame grid the term is +0, which leaves s and c unchanged
-        const T val = tm.in_j * (mu[b0 + bb] * acc);
-        const T t = s + val;
-        c += fabs(s) >= fabs(val) ? (s - t) + val : (val - t) + s;
-        s = t;
-      };
-      int bb = 0;
-      for (; bb + 4 <= nbc; bb += 4) {
-        Term tm[4];
+      } else {
+        const GatherCol<T>& c = cols[e0];
+        const T* base = Dfan + (size_t)uniform(c.b) * cp_elems;
+        for (int j = lane; j < g.Nv; j += 64) {
+          T r = T(0);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) fetch(bb + u, tm[u]);
+          for (int cc = 0; cc < 4; ++cc) r += c.w[cc] * base[uniform(c.off[cc]) + j];
+          rows[GATHER_PAD + j] = r;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int u = 0; u < 4; ++u) add(bb + u, tm[u]);
+      for (int u = 0; u < UU; ++u) {
+        const T q = cols[e0 + u].q;
+        const T* row = rows + u * pitch + GATHER_PAD;
+#pragma unroll
+        for (int s = 0; s < ZS; ++s) {
+          const T fjv = tz[s] * q + g.cv;
+          const T fj = dfloor(fjv), wj = fjv - fj;
+          // outside the plane both words are zero
+          const int j = min(max((int)fj, -GATHER_PAD), g.Nv);
+          const T lo = row[j], hi = row[j + 1];
+          sum[s].add(lo + wj * (hi - lo));
+        }
       }
-      for (; bb < nbc; ++bb) {
-        Term tm;
-        fetch(bb, tm);
-        add(bb, tm);
-      }
-    }
+      __builtin_amdgcn_wave_barrier();
+    };
+    int e = 0;
+    for (; e + U <= n; e += U) take(e, std::integral_constant<int, U>());
+    if constexpr (U > 1)
+      for (; e < n; ++e) take(e, std::integral_constant<int, 1>());
   }
-  if (!active) return;
-  if (last) {
-    dose[vox] = g.calib * (s + c);
-  } else {
-    dose[vox] = s;
-    comp[vox] = c;
+  const bool any_bad = __ballot(bad) != 0;  // (over the whole wavefront, before lanes past nz drop out)
+#pragma unroll
+  for (int s = 0; s < ZS; ++s) {
+    const int z = z0 + 64 * s;
+    if (z >= g.nz) continue;
+    const size_t vox = ((size_t)z * g.ny + y) * g.nx + x;
+    if (any_bad) sum[s].add(T(__builtin_nanf("")));
+    if (last)
+      dose[vox] = sum[s].value(g.calib);
+    else
+      sum[s].store(dose + vox, comp + vox);
   }
+}
+
+template <typename T, int JS, int ZS>
+static hipError_t launch_gather_cfg(const Geo<T>& g, int nb, int first, int last, const T* frame, const T* mu,
+                                    const T* Dfan, T* dose, T* comp, hipStream_t s) {
+  // Two control points in flight: four need more registers and lose more to the lower
+  // occupancy than they hide (128^3: 0.58 ms against 0.43); one: 0.40, but 0.11 against
+  // 0.09 on the 43-wide planes.  2 x 2 patches of independent wavefronts: 0.41 against
+  // 0.43 with 4 x 4 (192 x 192 x 128: 0.51 against 0.56).
+  constexpr int PX = 2, PY = 2, U = JS == 0 || sizeof(T) == 8 ? 1 : 2;
+  const int zc = (g.nz + 64 * ZS - 1) / (64 * ZS), xc = (g.nx + PX - 1) / PX, yc = (g.ny + PY - 1) / PY;
+  const long nblk = (long)zc * xc * yc;
+  if (nblk > 0x7ffffff0L) return hipErrorInvalidConfiguration;
+  const int js = JS ? JS : (g.Nv + 63) / 64;
+  const size_t lds = (size_t)PX * PY * (GATHER_CHUNK * sizeof(GatherCol<T>) + U * (64 * js + 2 * GATHER_PAD) * sizeof(T));
+  if (lds > 160 * 1024) return hipErrorInvalidConfiguration;
+  const void* kern = (const void*)k_gather<T, JS, ZS, PX, PY, U>;
+  {
+    hipError_t e = ensure_lds_limit(kern, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  const int grid = (int)((nblk + 7) / 8 * 8);
+  hipLaunchKernelGGL((k_gather<T, JS, ZS, PX, PY, U>), dim3(grid), dim3(64 * PX * PY), lds, s, g, nb, first, last, zc,
+                     xc, yc, frame, mu, Dfan, dose, comp);
+  return hipGetLastError();
+}
+
+template <typename T, int JS>
+static hipError_t launch_gather_js(const Geo<T>& g, int nb, int first, int last, const T* frame, const T* mu,
+                                   const T* Dfan, T* dose, T* comp, hipStream_t s) {
+  if (g.nz <= 64) return launch_gather_cfg<T, JS, 1>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
+  if (g.nz <= 128) return launch_gather_cfg<T, JS, 2>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
+  return launch_gather_cfg<T, JS, 3>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
 }
 
 template <typename T>
 hipError_t launch_gather(const Geo<T>& g, int nb, int first, int last, const T* frame, const T* mu, const T* Dfan,
                          T* dose, T* comp, hipStream_t s) {
-  const int zc = (g.nz + 63) / 64, xc = (g.nx + GATHER_P - 1) / GATHER_P, yc = (g.ny + GATHER_P - 1) / GATHER_P;
-  const long nblk = (long)zc * xc * yc;
-  if (nblk > 0x7ffffff0L) return hipErrorInvalidConfiguration;
   if ((long)g.Nk * g.Nu * g.Nv > 0x7fffffffL) return hipErrorInvalidConfiguration;  // 32-bit corner offsets
-  const int grid = (int)((nblk + 7) / 8 * 8);
-  hipLaunchKernelGGL(k_gather<T>, dim3(grid), dim3(64 * GATHER_NW), 0, s, g, nb, first, last, zc, xc, yc, frame, mu,
-                     Dfan, dose, comp);
-  return hipGetLastError();
+  if (g.Nv <= 64) return launch_gather_js<T, 1>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
+  if (g.Nv <= 128) return launch_gather_js<T, 2>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
+  if (g.Nv <= 192) return launch_gather_js<T, 3>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
+  if (g.Nv <= 256) return launch_gather_js<T, 4>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
+  return launch_gather_js<T, 0>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
 }
 
 #define PDRT_INST(T)                                                                                         \
