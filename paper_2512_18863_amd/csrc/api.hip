@@ -273,11 +273,13 @@ struct FcTaps {
 };
 
 template <typename T>
-void make_fc_taps(const pdrt_kernel_spec* spec, FcTaps<T>* t) {
+void make_fc_taps(const pdrt_kernel_spec* spec, FcTaps<T>* t, Geo<T>* g) {
   const double D = spec->lateral_step_mm;
   gauss_taps<T>(spec->pen_fwhm_mm[0] / kFwhmPerSigma, D, &t->pu);
   gauss_taps<T>(spec->pen_fwhm_mm[1] / kFwhmPerSigma, D, &t->pv);
   gauss_taps<T>(spec->hs_sigma_mm, D, &t->hs);
+  g->box_du = t->pu.R + t->hs.R;
+  g->box_dv = t->pv.R + t->hs.R;
 }
 
 #define CHECK_HIP(x)                    \
@@ -405,14 +407,13 @@ int forward_impl(const pdrt_grid* grid, const T* rho, const pdrt_beam* beam, con
   T* t0 = (T*)(w + P.lay.fc_tmp);
   T* t1 = t0 + (size_t)P.batch * P.Nu * P.Nv;
   FcTaps<T> fct;
-  if (g.fcorr) make_fc_taps<T>(spec, &fct);
+  if (g.fcorr) make_fc_taps<T>(spec, &fct, &g);
   int* box = (int*)(w + P.lay.box);
   // collimator rotation: F holds the collimator-frame map, Fb the beam-frame one
   const bool rot = beam->collimator_deg != nullptr;
   T* cframe = (T*)(w + P.lay.cframe);
   T* Fb = rot ? (T*)(w + P.lay.rot) : F;
   // the corrections spread the aperture's fluence by their blur radii
-  const int box_du = g.fcorr ? fct.pu.R + fct.hs.R : 0, box_dv = g.fcorr ? fct.pv.R + fct.hs.R : 0;
   // rays outside the box are skipped only when the convolution reads just the box
   const int* ray_box = conv_uses_box<T>(g, spec->conv_mode) ? box : nullptr;
   const T* dd = (const T*)spec->dd;
@@ -424,7 +425,7 @@ int forward_impl(const pdrt_grid* grid, const T* rho, const pdrt_beam* beam, con
     int nb = n_cp - cp0 < P.batch ? n_cp - cp0 : P.batch;
     const T* fr = frame + 2 * cp0;
     LAUNCH("raster", launch_raster<T>(g, nb, leaves + (size_t)2 * L * cp0, jaws + (size_t)4 * cp0, F, s));
-    LAUNCH("aperture_box", launch_aperture_box<T>(g, nb, jaws + (size_t)4 * cp0, box_du, box_dv, box, s));
+    LAUNCH("aperture_box", launch_aperture_box<T>(g, nb, jaws + (size_t)4 * cp0, g.box_du, g.box_dv, box, s));
     if (g.fcorr) {
       // F1 = G_v G_u F; F <- O (F1 + a G_hv G_hu F1)
       LAUNCH("fluence_corr", launch_blur<T>(g, nb, 0, fct.pu, F, t0, s));
@@ -480,7 +481,7 @@ int backward_impl(const pdrt_grid* grid, const T* rho, const pdrt_beam* beam, co
   T* t0 = (T*)(w + P.lay.fc_tmp);
   T* t1 = t0 + (size_t)P.batch * P.Nu * P.Nv;
   FcTaps<T> fct;
-  if (g.fcorr) make_fc_taps<T>(spec, &fct);
+  if (g.fcorr) make_fc_taps<T>(spec, &fct, &g);
   int* box = (int*)(w + P.lay.box);
   // collimator rotation: the march's adjoint gives dL/d(beam-frame map) in Ab, its
   // transpose through the rotation the collimator-frame A the rest reads
@@ -489,7 +490,6 @@ int backward_impl(const pdrt_grid* grid, const T* rho, const pdrt_beam* beam, co
   T* Ab = rot ? (T*)(w + P.lay.rot) : A;
   // the parameter gradients read A inside the aperture rectangle; the corrections'
   // adjoint gathers it from as far as their blur radii
-  const int box_du = g.fcorr ? fct.pu.R + fct.hs.R : 0, box_dv = g.fcorr ? fct.pv.R + fct.hs.R : 0;
   // with a box-restricted convolution H is valid only inside the box
   const int* ray_box = conv_uses_box<T>(g, spec->conv_mode) ? box : nullptr;
   const T* dd = (const T*)spec->dd;
@@ -506,7 +506,7 @@ int backward_impl(const pdrt_grid* grid, const T* rho, const pdrt_beam* beam, co
       if (gc) zb = gc->z + (size_t)cp0 * g.Nk;
     }
     if (!gc) LAUNCH("ca_depth", launch_ca_depth<T>(g, nb, fr, rho_t, z, s));
-    LAUNCH("aperture_box", launch_aperture_box<T>(g, nb, jaws + (size_t)4 * cp0, box_du, box_dv, box, s));
+    LAUNCH("aperture_box", launch_aperture_box<T>(g, nb, jaws + (size_t)4 * cp0, g.box_du, g.box_dv, box, s));
     if (rot) LAUNCH("collimator", launch_collimator_box<T>(g, nb, cframe + 2 * cp0, box, s));
     LAUNCH("backproject_adj", launch_backproject_adj<T>(g, nb, fr, g_t, vol0, s));
     LAUNCH(conv_name<T>(g, spec->conv_mode, 1),

@@ -246,6 +246,11 @@ __device__ __forceinline__ void put_win(const float* __restrict__ src, const Geo
   }
 }
 
+// Workgroup barrier for data in LDS only: waits for this wavefront's LDS accesses, not
+// (as __syncthreads does) for its global loads and stores in flight, so a persistent
+// workgroup starts its next plane while the last one's results are still on their way.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 inline int device_cus() {
   static int cached[64] = {0};
   int dev = 0;

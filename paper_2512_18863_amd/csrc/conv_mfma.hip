@@ -1238,10 +1238,8 @@ static hipError_t launch_f32_adj_win(const Geo<float>& g, const AdjWin& aw, int 
 hipError_t launch_conv_mfma_f32(const Geo<float>& g, int nb, const float* z, const float* in, float* out,
                                 hipStream_t s, const int* box, int support) {
   const int4* bx = reinterpret_cast<const int4*>(box);
-  // the forward with the rectangle in registers, unless the fluence corrections
-  // widen the rectangles by their blur radii (then several chunks per plane would
-  // repeat the tap loop; the tiled kernel below is faster there)
-  if (bx && support == CONV_IN_BOX && !g.fcorr && conv_fwd_reg_supported(g, false))
+  // the forward with the rectangle in registers (h <= 31)
+  if (bx && support == CONV_IN_BOX && conv_fwd_reg_supported(g, false))
     return launch_conv_fwd_reg(g, nb, z, in, out, s, box, false);
   // the adjoint with a window image, unless the fluence corrections widen the
   // rectangles past the field limits its pieces are sized for (then each rectangle

@@ -134,9 +134,10 @@ hipError_t launch_raster(const Geo<T>& g, int nb, const T* leaves, const T* jaws
 
 // Rectangle of fluence pixels [u0, u1) x [v0, v1) of each control point outside
 // which F and all its derivatives are exactly zero: a pixel carries fluence only
-// if it overlaps the jaw opening (the factor f(u; x1, x2) f(v; y1, y2) of Eq. 4),
-// widened by one pixel for rounding and by (du, dv) pixels for the reach of the
-// fluence corrections.  A non-finite jaw gives the whole plane.
+// if it overlaps the jaw opening (the factor f(u; x1, x2) f(v; y1, y2) of Eq. 4): pixel
+// i overlaps [a, b] iff fa < i < fb, with a thousandth of a pixel for rounding (indices
+// stay below 2^12, so theirs is below 2^-11), widened by (du, dv) pixels for the reach
+// of the fluence corrections.  A non-finite jaw gives the whole plane.
 template <typename T>
 __device__ __forceinline__ void pixel_range(T a, T b, T c, int N, int d, T inv_lat, int* lo, int* hi) {
   const T fa = a * inv_lat + c - T(0.5), fb = b * inv_lat + c + T(0.5);
@@ -145,7 +146,7 @@ __device__ __forceinline__ void pixel_range(T a, T b, T c, int N, int d, T inv_l
     *hi = N;
     return;
   }
-  int l = (int)floor(fa) - 1 - d, u = (int)ceil(fb) + 1 + d;
+  int l = (int)floor(fa - T(1e-3)) + 1 - d, u = (int)ceil(fb + T(1e-3)) + d;
   l = max(l, 0);
   u = min(u, N);
   *lo = l;

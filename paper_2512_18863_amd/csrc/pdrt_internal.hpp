@@ -45,6 +45,7 @@ struct Geo {
   // fluence corrections (off when fcorr == 0); the blur taps travel separately
   int fcorr;
   T hs_amp, oar0, oar1;
+  int box_du, box_dv;  // pixels by which the corrections widen the aperture rectangle along u and v
   // ray march: 0 = one thread per ray (serial), 1 = segmented scan across wavefronts
   int march_scan;
 };
