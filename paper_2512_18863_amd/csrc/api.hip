@@ -1,6 +1,7 @@
 // api.hip — the C ABI declared in include/pdrt.h: validation, beam-frame sizing,
 // workspace layout and the launch sequence of the dose path.  Host code only; it
 // never allocates, frees or synchronises.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -266,6 +267,18 @@ void make_geo(const pdrt_grid* grid, const pdrt_beam* beam, const pdrt_kernel_sp
   g->march_scan = spec->march_scan;
 }
 
+// Rectangle sizes the convolutions are shaped for: with collimator angles the field
+// limit along both axes is the hypotenuse, a rectangle w pixels wider on each side
+// reaches at most sqrt(2) w further when turned, and the turned rectangle takes two
+// pixels of margin.
+template <typename T>
+void bound_box(const pdrt_beam* beam, Geo<T>* g) {
+  g->conv_du = g->box_du;
+  g->conv_dv = g->box_dv;
+  if (beam->collimator_deg)
+    g->conv_du = g->conv_dv = (int)std::ceil(std::sqrt(2.0) * (std::max(g->box_du, g->box_dv) + 1)) + 2;
+}
+
 // The three Gaussians of the fluence corrections: penumbra along u and v, head scatter.
 template <typename T>
 struct FcTaps {
@@ -408,6 +421,7 @@ int forward_impl(const pdrt_grid* grid, const T* rho, const pdrt_beam* beam, con
   T* t1 = t0 + (size_t)P.batch * P.Nu * P.Nv;
   FcTaps<T> fct;
   if (g.fcorr) make_fc_taps<T>(spec, &fct, &g);
+  bound_box(beam, &g);
   int* box = (int*)(w + P.lay.box);
   // collimator rotation: F holds the collimator-frame map, Fb the beam-frame one
   const bool rot = beam->collimator_deg != nullptr;
@@ -482,6 +496,7 @@ int backward_impl(const pdrt_grid* grid, const T* rho, const pdrt_beam* beam, co
   T* t1 = t0 + (size_t)P.batch * P.Nu * P.Nv;
   FcTaps<T> fct;
   if (g.fcorr) make_fc_taps<T>(spec, &fct, &g);
+  bound_box(beam, &g);
   int* box = (int*)(w + P.lay.box);
   // collimator rotation: the march's adjoint gives dL/d(beam-frame map) in Ab, its
   // transpose through the rotation the collimator-frame A the rest reads

@@ -1,0 +1,272 @@
+// conv_adj.hip — the adjoint per-plane lateral convolution (arXiv:2512.18863 §2.2.6,
+// Eq. 8) on the CDNA4 BF16 matrix instructions, in FP32 (operands as three BF16 pieces)
+// or with BF16 operands, for outputs that are needed
+// inside the aperture rectangle only (the parameter gradients read them there).
+//
+// out[i][j] = sum_{p,q} K[p][q] in[i+p][j+q] = sum_{p >= 0} sum_c K[p][c - j] S_p[i][c],
+//   S_p[i][c] = in[i+p][c] + in[i-p][c]   (the taps are even in p; row 0 counts half),
+// a product per tap row p with M = 16 output columns j, N = 16 output rows i and K = 32
+// plane columns c (a group):
+//   A[m][k] = K[p][c_k - j_m] (from the extended tap row), B[k][n] = S_p[i_n][c_k].
+// The window of plane rows and columns that a piece of T x CB output tiles reads sits
+// in LDS in FP32; a wavefront forms S_p in FP32 and splits it, like the taps, exactly
+// into three BF16 pieces (see conv_fwd_reg.hip: six piece products per product, each
+// exact, FP32 sums).  Folding the two rows first halves the matrix work; the split is
+// done in the vector unit, which the matrix instructions leave free.
+//
+// One workgroup per (control point, plane) item and piece; its wavefronts share the
+// (column group, tap row) pairs evenly, each for all T x CB tiles, so a split feeds CB
+// tiles and a tap run T.  Their sums are added in LDS in wavefront order, one row of
+// tiles at a time.  (Wavefronts come in multiples of four: a workgroup of six, two on
+// two of the SIMDs, kept a second one off the compute unit.)
+//
+// A lane's K entries of a group are columns 4 kk + 0..3 and 16 + 4 kk + 0..3 (A and B
+// agree), so that its image reads are two 16-byte reads at n P + 4 kk words, free of
+// bank conflicts for a pitch P of 8 (mod 16) words.
+//
+// What bounds it: vector instructions, 52 per S_p fragment beside 12 to 24 matrix
+// instructions of 16 cycles.  FP32 against the windowed kernel on FP32 matrix
+// instructions (conv_mfma.hip, which remains for h > 31): 180 control points at 128^3 (n
+// = 61, 27 x 27 outputs) 1.33 ms (1.61), at 224 x 224 x 105 (n = 55, 41 x 41) 3.3 ms
+// (5.8), at 192 x 192 x 128 (n = 31) 0.90 ms (1.15), 90 at 128 x 128 x 96 (n = 15) 0.13 ms
+// (0.22); 90 with fluence corrections and collimator rotation (up to 99 x 99) 7.0 ms
+// (9.1 by regions).  BF16: 1.8 ms on the second (2.9), 0.086 on the fourth (0.14), 3.8
+// on the last (13).
+#include <type_traits>
+
+#include "conv_common.hpp"
+
+namespace pdrt {
+
+namespace {
+
+typedef float f32x4a __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4a __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8a __attribute__((ext_vector_type(8)));
+typedef float f32x4ua __attribute__((ext_vector_type(4), aligned(4)));
+
+__host__ __device__ inline int adj_img_rows(int T, int h) { return 16 * T + 2 * h; }
+
+// NP pieces per operand: 3 (FP32) or 1 (BF16; the rows are then not folded).
+template <int NP, int T, int CB>
+__global__ void __launch_bounds__(512, T <= 2 ? 5 : T == 3 ? 4 : 2) k_conv_adj(Geo<float> g, int pitch, const int4* __restrict__ box,
+                                                      const float* __restrict__ zca, const float* __restrict__ in,
+                                                      float* __restrict__ out) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int h = g.h, h1 = h + 1, rows = adj_img_rows(T, h);
+  const int CS = h1 * NP * kRegW;
+  unsigned* taps = reinterpret_cast<unsigned*>(smem_raw);
+  float* img = reinterpret_cast<float*>(taps + reg_tap_words(h, NP));
+  f32x4a* sums = reinterpret_cast<f32x4a*>(img);  // [wavefront][CB][64], once the image is no longer read
+  const int NT = blockDim.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = NT >> 6;
+  const int bk = blockIdx.x;
+  const int b = bk / g.Nk, k = bk - b * g.Nk;
+  const int Nu = g.Nu, Nv = g.Nv;
+  const size_t plane = (size_t)Nu * Nv;
+  const int4 bx = box[b];
+  const int r0 = max(bx.x, 0), r1 = min(bx.y, Nu), c0 = max(bx.z, 0), c1 = min(bx.w, Nv);
+  if (r1 <= r0 || c1 <= c0) return;
+  const int npi = (r1 - r0 + 16 * T - 1) / (16 * T), npj = (c1 - c0 + 16 * CB - 1) / (16 * CB);
+  if ((int)blockIdx.y >= npi * npj) return;
+  const float* src = in + (size_t)bk * plane;
+  float* dst = out + (size_t)bk * plane;
+  const int n = lane & 15, kk = lane >> 4;
+  clear_tap_rows(taps, h, NP, tid, NT);
+  bool built = false;
+
+  for (int pp = blockIdx.y; pp < npi * npj; pp += gridDim.y) {
+    const int I = r0 + 16 * T * (pp / npj), J = c0 + 16 * CB * (pp % npj);
+    // the window: plane rows I - h + [0, rows), columns wc0 + [0, 32 ng), zero outside the
+    // plane; a four-column group that starts inside a row may read up to three words past
+    // its end (the next row, or after the batch's last row the workspace that follows)
+    const int wc0 = max(0, J - h), wc1 = min(Nv, min(J + 16 * CB, c1) + h);
+    const int ng = (wc1 - wc0 + 31) / 32, gw = 8 * ng;
+    for (RectWalk w(tid, NT, gw); w.r < rows; w.next(gw)) {
+      const int r = w.r, q = w.c;
+      const int pr = I - h + r, pc = wc0 + 4 * q;
+      f32x4a v = {0.f, 0.f, 0.f, 0.f};
+      if (pr >= 0 && pr < Nu && pc < Nv) {
+        const f32x4ua x = *reinterpret_cast<const f32x4ua*>(src + (size_t)pr * Nv + pc);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = pc + c < Nv ? x[c] : 0.f;
+      }
+      *reinterpret_cast<f32x4a*>(img + r * pitch + 4 * q) = v;
+    }
+    if (!built) {
+      lds_barrier();  // the rows are cleared
+      build_tap_rows<NP>(g, k, zca[bk], taps, tid, NT, 0.5f);
+      built = true;
+    }
+    lds_barrier();
+
+    f32x4a acc[T][CB];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int c = 0; c < CB; ++c) acc[t][c] = f32x4a{0.f, 0.f, 0.f, 0.f};
+    // all the pairs (gq, p), p fastest, of this wavefront, for TT x CC tiles
+    auto products = [&](auto tt, auto cb) {
+      constexpr int TT = decltype(tt)::value, CC = decltype(cb)::value;
+      const int ua = ng * h1 * wave / nw, uz = ng * h1 * (wave + 1) / nw;
+      for (int gq = ua / h1; gq * h1 < uz; ++gq) {
+        const int pa = max(ua - gq * h1, 0), pz = min(uz - gq * h1, h1);
+        // tap runs of the lane: four taps each for columns 4 kk and 16 + 4 kk of the group, a
+        // run that meets no tap moved to the zeros beside them
+        const unsigned* run[CC][2];
+#pragma unroll
+        for (int c = 0; c < CC; ++c)
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            int x = kRegOff + wc0 + 32 * gq + 16 * e + 4 * kk - (J + 16 * c + n);
+            const int x0 = kRegOff - h - 5, x1 = kRegOff + h + 1;
+            if (x < x0 + 1) x = x0 + ((x ^ x0) & 1);
+            if (x > x1) x = x1 + ((x ^ x1) & 1);
+            run[c][e] = taps + ((x & 1) ? CS : 0) + (x >> 1) + pa * NP * kRegW;
+          }
+        const float* up = img + (n + h + pa) * pitch + 32 * gq + 4 * kk;
+        const float* dn = img + (n + h - pa) * pitch + 32 * gq + 4 * kk;
+#pragma unroll 1
+        for (int p = pa; p < pz; ++p) {
+          u32x4a A[CC][NP];
+#pragma unroll
+          for (int c = 0; c < CC; ++c)
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+              A[c][i] = u32x4a{run[c][0][i * kRegW], run[c][0][i * kRegW + 1], run[c][1][i * kRegW],
+                               run[c][1][i * kRegW + 1]};
+#pragma unroll
+          for (int t = 0; t < TT; ++t) {
+            // FP32: the pieces of the folded rows; BF16: the rows i + p and i - p rounded
+            // one by one, so that every input is rounded by itself
+            constexpr int NB = NP == 3 ? 3 : 2;
+            u32x4a B[NB];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const f32x4a x = *reinterpret_cast<const f32x4a*>(up + 16 * t * pitch + 16 * e),
+                           y = *reinterpret_cast<const f32x4a*>(dn + 16 * t * pitch + 16 * e);
+#pragma unroll
+              for (int w = 0; w < 2; ++w) {
+                if constexpr (NP == 3) {
+                  unsigned u[NP];
+                  reg_pieces2<NP>(x[2 * w] + y[2 * w], x[2 * w + 1] + y[2 * w + 1], u);
+#pragma unroll
+                  for (int i = 0; i < NP; ++i) B[i][2 * e + w] = u[i];
+                } else {
+                  unsigned u[1];
+                  reg_pieces2<1>(x[2 * w], x[2 * w + 1], u);
+                  B[0][2 * e + w] = u[0];
+                  reg_pieces2<1>(y[2 * w], y[2 * w + 1], u);
+                  B[1][2 * e + w] = u[0];
+                }
+              }
+            }
+            // (piece of A, piece of B), smallest products first
+            constexpr int np = NP == 3 ? 6 : 2, qa[6] = {2, 0, 1, 1, 0, 0}, qb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int i = 0; i < np; ++i)
+#pragma unroll
+              for (int c = 0; c < CC; ++c)
+                acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8a, A[c][NP == 3 ? qa[i] : 0]),
+                    __builtin_bit_cast(bf16x8a, B[NP == 3 ? qb[i] : i]), acc[t][c], 0, 0, 0);
+          }
+          up += pitch;
+          dn -= pitch;
+#pragma unroll
+          for (int c = 0; c < CC; ++c) {
+            run[c][0] += NP * kRegW;
+            run[c][1] += NP * kRegW;
+          }
+        }
+      }
+    };
+    // a rectangle (or its last piece) one row or column of tiles smaller leaves them out
+    typedef std::integral_constant<int, T> FT;
+    typedef std::integral_constant<int, (T > 1 ? T - 1 : 1)> ST;
+    typedef std::integral_constant<int, CB> FC;
+    typedef std::integral_constant<int, (CB > 1 ? CB - 1 : 1)> SC;
+    const bool st = r1 - I <= 16 * (T - 1), sc = c1 - J <= 16 * (CB - 1);
+    if (st) {
+      if (sc) products(ST(), SC());
+      else products(ST(), FC());
+    } else {
+      if (sc) products(FT(), SC());
+      else products(FT(), FC());
+    }
+    // the wavefronts' sums, one row of tiles at a time; lane (n, kk) holds output row n
+    // and columns 4 kk + e of a tile
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      lds_barrier();
+#pragma unroll
+      for (int c = 0; c < CB; ++c) sums[(wave * CB + c) * 64 + lane] = acc[t][c];
+      lds_barrier();
+      for (int c = wave; c < CB; c += nw) {
+        f32x4a v = sums[c * 64 + lane];
+        for (int w = 1; w < nw; ++w) v += sums[(w * CB + c) * 64 + lane];
+        const int i = I + 16 * t + n, j = J + 16 * c + 4 * kk;
+        if (i < Nu) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (j + e < Nv) dst[(size_t)i * Nv + j + e] = v[e];
+        }
+      }
+    }
+    lds_barrier();  // the next piece's window overwrites the sums
+  }
+}
+
+template <int NP, int N>
+hipError_t launch_adj_cfg(const Geo<float>& g, int nb, int pieces, const int4* box, const float* z, const float* in,
+                          float* out, hipStream_t s) {
+  const int pitch = (min(g.Nv, 16 * N + 2 * g.h) + 31) / 32 * 32 + 8;
+  const int nw = g.h <= 16 ? 4 : 8;
+  const size_t img = sizeof(float) * (size_t)adj_img_rows(N, g.h) * pitch, red = (size_t)nw * N * 1024;
+  const size_t lds = sizeof(unsigned) * (size_t)reg_tap_words(g.h, NP) + (img > red ? img : red);
+  if (lds > 160 * 1024) return hipErrorInvalidConfiguration;
+  const void* kern = (const void*)k_conv_adj<NP, N, N>;
+  {
+    hipError_t e = ensure_lds_limit(kern, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  const long n_items = (long)nb * g.Nk;
+  if (n_items > 0x7fffffffL) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL((k_conv_adj<NP, N, N>), dim3((unsigned)n_items, pieces), dim3(64 * nw), lds, s, g, pitch, box, z, in,
+                     out);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool conv_adj_supported(const Geo<float>& g) { return g.h >= 1 && g.h <= kRegMaxH; }
+
+// Pieces of N x N tiles for the largest rectangle that jaws inside the field limits
+// give, widened by fluence corrections and collimator rotation (N <= 4; equal pieces); a rectangle
+// larger than that has its workgroups take several pieces.
+hipError_t launch_conv_adj(const Geo<float>& g, int nb, const float* z, const float* in, float* out, hipStream_t s,
+                           const int* box, bool bf16) {
+  if (!conv_adj_supported(g) || !box) return hipErrorInvalidConfiguration;
+  const int4* bx = reinterpret_cast<const int4*>(box);
+  const int half_u = (g.Nu - 1) / 2 - g.h, half_v = (g.Nv - 1) / 2 - g.h;  // field limit in pixels
+  const int br = min(g.Nu, 2 * (half_u > 0 ? half_u : 0) + 1 + 2 * g.conv_du);
+  const int bc = min(g.Nv, 2 * (half_v > 0 ? half_v : 0) + 1 + 2 * g.conv_dv);
+  const int blocks = ((br > bc ? br : bc) + 15) / 16, per = (blocks + 3) / 4, n = (blocks + per - 1) / per;
+  const int pieces = ((br + 16 * n - 1) / (16 * n)) * ((bc + 16 * n - 1) / (16 * n));
+  if (bf16) {
+    switch (n) {
+      case 1: return launch_adj_cfg<1, 1>(g, nb, pieces, bx, z, in, out, s);
+      case 2: return launch_adj_cfg<1, 2>(g, nb, pieces, bx, z, in, out, s);
+      case 3: return launch_adj_cfg<1, 3>(g, nb, pieces, bx, z, in, out, s);
+      default: return launch_adj_cfg<1, 4>(g, nb, pieces, bx, z, in, out, s);
+    }
+  }
+  switch (n) {
+    case 1: return launch_adj_cfg<3, 1>(g, nb, pieces, bx, z, in, out, s);
+    case 2: return launch_adj_cfg<3, 2>(g, nb, pieces, bx, z, in, out, s);
+    case 3: return launch_adj_cfg<3, 3>(g, nb, pieces, bx, z, in, out, s);
+    default: return launch_adj_cfg<3, 4>(g, nb, pieces, bx, z, in, out, s);
+  }
+}
+
+}  // namespace pdrt

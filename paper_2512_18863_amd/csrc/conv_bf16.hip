@@ -682,8 +682,16 @@ hipError_t launch_conv_mfma_bf16(const Geo<float>& g, int nb, const float* z, co
                                  hipStream_t s, const int* box, int support) {
   const int4* bx = reinterpret_cast<const int4*>(box);
   if (support == CONV_OUT_BOX && bx) {
-    // the windowed adjoint, unless the fluence corrections widen the rectangles (as
-    // for FP32, the tiled kernel's chunks serve them)
+    // rectangles of at most 2 x 2 tiles with a wide kernel: the windowed adjoint below (128^3
+    // plan, n = 61: 0.57 against 0.65 ms); small kernels and larger rectangles: the FP32
+    // adjoint's form (n = 15: 0.086 against 0.14 ms; 41 x 41 pixels, n = 55: 1.8 against 2.9
+    // ms; with fluence corrections and collimator rotation 3.8 against 13 ms)
+    const int half = (max(g.Nu, g.Nv) - 1) / 2 - g.h;  // field limit in pixels
+    const bool small_box = !g.fcorr && 2 * half + 1 + 2 * max(g.conv_du, g.conv_dv) <= 32;
+    if (conv_adj_supported(g) && !(small_box && g.h > 16))
+      return launch_conv_adj(g, nb, z, in, out, s, box, true);
+    // the windowed adjoint, unless the fluence corrections widen the rectangles (for h > 31
+    // the tiled kernel's chunks serve them)
     hipError_t e;
     if (!g.fcorr && launch_bf16_adj_win(g, nb, bx, z, in, out, s, &e)) return e;
     return launch_bf16_sup<CONV_OUT_BOX>(g, nb, bx, z, in, out, s);

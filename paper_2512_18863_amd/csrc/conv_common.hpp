@@ -1,8 +1,8 @@
 // conv_common.hpp — staging helpers shared by the per-plane lateral convolutions
 // (arXiv:2512.18863 §2.2.6, Eq. 8): the unique taps of a plane, the rectangle of a
 // plane that one workgroup's LDS image holds, register prefetch of the next
-// plane, the windowed adjoints' staging in four-column groups, and the grid of a
-// persistent launch.
+// plane, the windowed adjoints' staging in four-column groups, the BF16 tap rows of
+// the matrix kernels, and the grid of a persistent launch.
 #pragma once
 
 #include "taps.hpp"
@@ -243,6 +243,76 @@ __device__ __forceinline__ void put_win(const float* __restrict__ src, const Geo
   for (int r = st.r0 + PG * st.step; r < w.nr; r += st.step) {
     const f32x4 v = edge ? load_group<true>(src, g, w, st, r) : load_group<false>(src, g, w, st, r);
     *reinterpret_cast<f32x4*>(tile + r * pitch + 4 * st.cg) = mask_group(g, w, st, r, v);
+  }
+}
+
+constexpr int kRegMaxH = 31;  // widest kernel half-width served
+
+// BF16 tap rows (FP32 taps as three BF16 pieces).  Element x of extended tap row p holds
+// K[p][|x - kRegOff|] for |x - kRegOff| <= h, else 0.  Each lane reads a run of eight taps; a run wholly left or right of the taps is
+// moved to the nearest run of zeros that starts with its parity (two margins of nine
+// elements hold them).  A row is two copies of BF16 pairs, the second shifted by one
+// tap, so that every run is four aligned words.  Rows have the length of the widest
+// kernel served, so that a lane's reads of one row are one address and constant
+// offsets: copy c, row p, piece i starts at word ((c (h + 1) + p) NP + i) kRegW.
+constexpr int kRegOff = kRegMaxH + 9;
+constexpr int kRegW = (kRegOff + kRegMaxH + 10 + 1) / 2;
+
+// The NP BF16 pieces of a pair, packed (a in the low half-words): piece i is the rounded
+// remainder of the ones before, so three of them hold an FP32 number exactly.
+typedef __bf16 bf16x2_c __attribute__((ext_vector_type(2)));
+typedef float f32x2_c __attribute__((ext_vector_type(2)));
+template <int NP>
+__device__ __forceinline__ void reg_pieces2(float a, float b, unsigned (&u)[NP]) {
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const f32x2_c x = {a, b};
+    u[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(x, bf16x2_c));
+    a -= __uint_as_float(u[i] << 16);
+    b -= __uint_as_float(u[i] & 0xffff0000u);
+  }
+}
+
+// LDS words of the tap rows: two copies of (h + 1) rows of NP pieces, and the row read
+// ahead after the last; a multiple of four.
+__host__ __device__ inline int reg_tap_words(int h, int np) { return ((2 * (h + 1) + 1) * np * kRegW + 3) & ~3; }
+
+__device__ __forceinline__ void clear_tap_rows(unsigned* lds, int h, int np, int tid, int nt) {
+  for (int i = tid; i < reg_tap_words(h, np) / 4; i += nt) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// The plane's taps into cleared rows: pair (p, q), p <= q, at its four places in both
+// copies (element x of a row is half-word x of copy 0 and half-word x - 1 of copy 1);
+// row 0 scaled by s0 (a power of two).
+template <int NP>
+__device__ __forceinline__ void build_tap_rows(const Geo<float>& g, int k, float zk, unsigned* lds, int tid, int nt,
+                                               float s0) {
+  const int h1 = g.h + 1, CS = h1 * NP * kRegW;
+  unsigned short* H0 = reinterpret_cast<unsigned short*>(lds);
+  const TapParams<float> tp = tap_params(g, k, zk);
+  for (int t = tid; t < h1 * (h1 + 1) / 2; t += nt) {
+    int q = (int)((sqrtf((float)(8 * t + 1)) - 1.f) * 0.5f);
+    if ((q + 1) * (q + 2) / 2 <= t) ++q;
+    if (q * (q + 1) / 2 > t) --q;
+    const int p = t - q * (q + 1) / 2;
+    const float v = tap_value(tp, p, q);
+    unsigned v2[NP];  // pieces in row p (low half-word) and in row q
+    reg_pieces2<NP>(p == 0 ? s0 * v : v, q == 0 ? s0 * v : v, v2);
+    const int rp = 2 * NP * kRegW * p + kRegOff, rq = 2 * NP * kRegW * q + kRegOff;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      unsigned short* P0 = H0 + 2 * kRegW * i;
+      unsigned short* P1 = P0 + 2 * CS - 1;
+      const unsigned short u = (unsigned short)v2[i], w = (unsigned short)(v2[i] >> 16);
+      P0[rp + q] = u;
+      P0[rp - q] = u;
+      P0[rq + p] = w;
+      P0[rq - p] = w;
+      P1[rp + q] = u;
+      P1[rp - q] = u;
+      P1[rq + p] = w;
+      P1[rq - p] = w;
+    }
   }
 }
 

@@ -50,9 +50,9 @@
 // What bounds it: the vector instructions of the row shifts (16 per product) beside
 // the matrix instructions (the two overlap: 16 cycles of matrix unit and about 7 of
 // issue per product).  180 control points at 128^3 (n = 61, 27 x 27 boxes, 32940
-// planes): FP32 1.03 ms (1.91 on FP32 matrix instructions), BF16 0.52 ms (0.65); 224 x
-// 224 x 105 (n = 55, 41 x 41): 3.2 ms (6.3); 90 control points with fluence corrections
-// and collimator rotation (n = 61, up to 99 x 99): 6.2 ms (24.9).
+// planes): FP32 0.92 ms (1.91 on FP32 matrix instructions), BF16 0.53 ms (0.65); 224 x
+// 224 x 105 (n = 55, 41 x 41): 3.0 ms (6.3); 90 control points with fluence corrections
+// and collimator rotation (n = 61, up to 99 x 99): 6.1 ms (24.9).
 #include "conv_common.hpp"
 
 namespace pdrt {
@@ -63,18 +63,8 @@ typedef __bf16 bf16x8r __attribute__((ext_vector_type(8)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any word address
 
 constexpr int kRegQB = 2;    // output blocks of 16 rows above and below a row chunk
-constexpr int kRegMaxH = 16 * (kRegQB - 1) + 15;  // largest half-width the blocks reach
 constexpr int kRegGW = 32;   // columns per group (one uniform branch each)
-
-// Extended tap row p: element x holds K[p][|x - kRegOff|] for |x - kRegOff| <= h, else
-// 0.  Each lane reads a run of eight taps; a run wholly left or right of the taps is
-// moved to the nearest run of zeros that starts with its parity (two margins of nine
-// elements hold them).  A row is two copies of BF16 pairs, the second shifted by one
-// tap, so that every run is four aligned words.  Rows have the length of the widest
-// kernel served, so that a lane's reads of one row are one address and constant
-// offsets: copy c, row p, piece i starts at word ((c (h + 1) + p) NP + i) kRegW.
-constexpr int kRegOff = kRegMaxH + 9;
-constexpr int kRegW = (kRegOff + kRegMaxH + 10 + 1) / 2;
+static_assert(16 * (kRegQB - 1) + 15 == kRegMaxH, "the blocks reach the largest half-width");
 
 // Lane i takes lane i + S (LEFT) or i - S of its 16-lane row; 0 where that lane lies
 // outside the row.  1 <= S <= 15.  (Each component is copied to a scalar before its
@@ -187,25 +177,9 @@ __device__ __forceinline__ void reg_tap_rows(int h, const unsigned* const (&aadd
   }
 }
 
-// The NP BF16 pieces of x.
-template <int NP>
-__device__ __forceinline__ void reg_pieces(float x, __bf16 (&p)[NP]) {
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    p[i] = (__bf16)x;
-    x -= (float)p[i];
-  }
-}
-
-__device__ __forceinline__ unsigned reg_bits(__bf16 v) { return *reinterpret_cast<const unsigned short*>(&v); }
-
-// LDS words of the tap rows: two copies of (h + 1) rows of NP pieces, and the row read
-// ahead after the last; a multiple of four.
-__host__ __device__ inline int reg_tap_words(int h, int np) { return ((2 * (h + 1) + 1) * np * kRegW + 3) & ~3; }
-
 // Wavefronts per SIMD the registers are kept for.
 __host__ __device__ constexpr int reg_waves(int np, int T) {
-  return np == 3 ? (T == 1 ? 6 : T == 2 ? 5 : T == 3 ? 3 : 2) : (T <= 2 ? 7 : T == 3 ? 4 : 3);
+  return np == 3 ? (T == 1 ? 6 : T == 2 ? 5 : T == 3 ? 3 : 2) : (T <= 2 ? 7 : T == 3 ? 4 : T == 4 ? 3 : 2);
 }
 
 // T: row blocks of 16 box rows per chunk; SU: column groups per chunk (boxes larger
@@ -267,48 +241,19 @@ __global__ void __launch_bounds__(512, reg_waves(NP, T)) k_conv_fwd_reg(Geo<floa
         const f32x4r x[2] = {run4(r, c), run4(r, c + 4)};
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-          __bf16 lo[NP], hi[NP];
-          reg_pieces<NP>(x[w / 2][2 * (w & 1)], lo);
-          reg_pieces<NP>(x[w / 2][2 * (w & 1) + 1], hi);
+          unsigned v[NP];
+          reg_pieces2<NP>(x[w / 2][2 * (w & 1)], x[w / 2][2 * (w & 1) + 1], v);
 #pragma unroll
-          for (int i = 0; i < NP; ++i) B[i][t][u][w] = reg_bits(lo[i]) | (reg_bits(hi[i]) << 16);
+          for (int i = 0; i < NP; ++i) B[i][t][u][w] = v[i];
         }
       }
     }
   };
   if (wave < njt) load_b(0, 0);  // in flight while the taps are built
 
-  // Element x of a row is half-word x of copy 0 and half-word x - 1 of copy 1.  The rows
-  // are cleared, then pair (p, q) is written to its four places in both copies.
-  for (int i = tid; i < reg_tap_words(h, NP) / 4; i += NT) reinterpret_cast<u32x4r*>(lds)[i] = u32x4r{0u, 0u, 0u, 0u};
+  clear_tap_rows(lds, h, NP, tid, NT);
   lds_barrier();
-  {
-    unsigned short* H0 = reinterpret_cast<unsigned short*>(lds);
-    const TapParams<float> tp = tap_params(g, k, zca[bk]);
-    for (int t = tid; t < h1 * (h1 + 1) / 2; t += NT) {
-      int q = (int)((sqrtf((float)(8 * t + 1)) - 1.f) * 0.5f);
-      if ((q + 1) * (q + 2) / 2 <= t) ++q;
-      if (q * (q + 1) / 2 > t) --q;
-      const int p = t - q * (q + 1) / 2;
-      __bf16 v[NP];
-      reg_pieces<NP>(tap_value(tp, p, q), v);
-      const int rp = 2 * NP * kRegW * p + kRegOff, rq = 2 * NP * kRegW * q + kRegOff;
-#pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        unsigned short* P0 = H0 + 2 * kRegW * i;
-        unsigned short* P1 = P0 + 2 * CS - 1;
-        const unsigned short u = (unsigned short)reg_bits(v[i]);
-        P0[rp + q] = u;
-        P0[rp - q] = u;
-        P0[rq + p] = u;
-        P0[rq - p] = u;
-        P1[rp + q] = u;
-        P1[rp - q] = u;
-        P1[rq + p] = u;
-        P1[rq - p] = u;
-      }
-    }
-  }
+  build_tap_rows<NP>(g, k, zca[bk], lds, tid, NT, 1.f);
   // With one chunk the strips are stored once and the plane outside them [wr0, wr1)
   // x [cw0, cw0 + 16 njt) is zero; with several the whole plane is cleared first
   // and the strips are added (the barrier below orders the clearing before them).
@@ -417,24 +362,30 @@ static hipError_t launch_reg_cfg(const Geo<float>& g, int nb, const int4* box, c
 template <int NP>
 static hipError_t launch_reg_np(const Geo<float>& g, int nb, const int4* box, const float* z, const float* in,
                                 float* out, hipStream_t s, int ch) {
-  if (ch <= 1) return launch_reg_cfg<NP, 1, 1>(g, nb, box, z, in, out, s);
-  if (ch == 2) return launch_reg_cfg<NP, 2, 1>(g, nb, box, z, in, out, s);
-  if (ch == 3) return launch_reg_cfg<NP, 3, 2>(g, nb, box, z, in, out, s);
-  return launch_reg_cfg<NP, 4, 2>(g, nb, box, z, in, out, s);
+  switch (ch) {
+    case 1: return launch_reg_cfg<NP, 1, 1>(g, nb, box, z, in, out, s);
+    case 2: return launch_reg_cfg<NP, 2, 1>(g, nb, box, z, in, out, s);
+    case 3: return launch_reg_cfg<NP, 3, 2>(g, nb, box, z, in, out, s);
+    case 4: return launch_reg_cfg<NP, 4, 2>(g, nb, box, z, in, out, s);
+    case 5: return launch_reg_cfg<NP, 5, 2>(g, nb, box, z, in, out, s);
+    default: return launch_reg_cfg<NP, 6, 2>(g, nb, box, z, in, out, s);
+  }
 }
 
 // The chunk shape from the largest rectangle that jaws inside the field limits give,
-// widened by the fluence corrections' radii; rectangles larger than a chunk are taken
-// in several, of four row blocks (rotated and widened to 99 x 99: 6.2 ms, with three
-// 6.8, with six blocks and three groups, one wavefront per SIMD, 9.3).
+// widened by fluence corrections and collimator rotation: one row chunk of up to six
+// blocks, else equal chunks; columns beyond two groups come in column chunks, summed in
+// registers.  (n = 61, 180 control points, 71 x 71 boxes: 5.4 ms with five blocks, 9.5 in
+// two chunks of four, 10.1 of three; all columns at once leave one wavefront per SIMD.)
 hipError_t launch_conv_fwd_reg(const Geo<float>& g, int nb, const float* z, const float* in, float* out,
                                hipStream_t s, const int* box, bool bf16) {
   if (!conv_fwd_reg_supported(g, bf16) || !box) return hipErrorInvalidConfiguration;
   const int4* bx = reinterpret_cast<const int4*>(box);
   const int half_u = (g.Nu - 1) / 2 - g.h, half_v = (g.Nv - 1) / 2 - g.h;  // field limit in pixels
-  const int br = min(g.Nu, 2 * (half_u > 0 ? half_u : 0) + 1 + 2 * g.box_du);
-  const int bc = min(g.Nv, 2 * (half_v > 0 ? half_v : 0) + 1 + 2 * g.box_dv);
-  const int ch = ((br > bc ? br : bc) + 15) / 16;
+  const int br = min(g.Nu, 2 * (half_u > 0 ? half_u : 0) + 1 + 2 * g.conv_du);
+  const int bc = min(g.Nv, 2 * (half_v > 0 ? half_v : 0) + 1 + 2 * g.conv_dv);
+  const int blocks = ((br > bc ? br : bc) + 15) / 16, chunks = (blocks + 5) / 6;
+  const int ch = (blocks + chunks - 1) / chunks;
   return bf16 ? launch_reg_np<1>(g, nb, bx, z, in, out, s, ch) : launch_reg_np<3>(g, nb, bx, z, in, out, s, ch);
 }
 

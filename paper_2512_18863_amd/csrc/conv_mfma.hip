@@ -1215,21 +1215,14 @@ static bool f32_adj_win_shape(const Geo<float>& g, AdjWin* out) {
 
 static hipError_t launch_f32_adj_win(const Geo<float>& g, const AdjWin& aw, int nb, const int4* box,
                                      const float* z, const float* in, float* out, hipStream_t s) {
-  // one or two tiles per wavefront; super-step counts 2 to 5 (h 1 to 32) unrolled,
-  // others looped
+  // one or two tiles per wavefront; five super-steps (h 32) unrolled, more looped
   if (aw.WI * aw.WJ <= kAdjWinNW) {
     switch (aw.SS) {
-      case 2: return launch_f32_adj_win_cfg<1, 2>(g, aw, nb, box, z, in, out, s);
-      case 3: return launch_f32_adj_win_cfg<1, 3>(g, aw, nb, box, z, in, out, s);
-      case 4: return launch_f32_adj_win_cfg<1, 4>(g, aw, nb, box, z, in, out, s);
       case 5: return launch_f32_adj_win_cfg<1, 5>(g, aw, nb, box, z, in, out, s);
       default: return launch_f32_adj_win_cfg<1, 0>(g, aw, nb, box, z, in, out, s);
     }
   }
   switch (aw.SS) {
-    case 2: return launch_f32_adj_win_cfg<2, 2>(g, aw, nb, box, z, in, out, s);
-    case 3: return launch_f32_adj_win_cfg<2, 3>(g, aw, nb, box, z, in, out, s);
-    case 4: return launch_f32_adj_win_cfg<2, 4>(g, aw, nb, box, z, in, out, s);
     case 5: return launch_f32_adj_win_cfg<2, 5>(g, aw, nb, box, z, in, out, s);
     default: return launch_f32_adj_win_cfg<2, 0>(g, aw, nb, box, z, in, out, s);
   }
@@ -1241,6 +1234,9 @@ hipError_t launch_conv_mfma_f32(const Geo<float>& g, int nb, const float* z, con
   // the forward with the rectangle in registers (h <= 31)
   if (bx && support == CONV_IN_BOX && conv_fwd_reg_supported(g, false))
     return launch_conv_fwd_reg(g, nb, z, in, out, s, box, false);
+  // the adjoint on the BF16 matrix instructions (h <= 31)
+  if (bx && support == CONV_OUT_BOX && conv_adj_supported(g))
+    return launch_conv_adj(g, nb, z, in, out, s, box, false);
   // the adjoint with a window image, unless the fluence corrections widen the
   // rectangles past the field limits its pieces are sized for (then each rectangle
   // takes several pieces whose windows overlap; the region kernel below stages its

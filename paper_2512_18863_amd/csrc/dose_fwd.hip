@@ -645,7 +645,7 @@ hipError_t launch_conv_direct(const Geo<T>& g, int nb, const T* z, const T* in, 
 // (k + 1, i), (k + 1, i + 1) are first blended into one row over j, which its z then
 // read at j0 and j0 + 1.  One wavefront owns a column and ZS z per lane (lanes along
 // z): its lanes load the four rows coalesced (lanes along j), blend them with the
-// corner weights (times MU) and park the blended row in LDS; every z then takes two
+// corner weights and park the blended row in LDS; every z then takes two
 // neighbouring words of it.  A control point whose fan misses the column is skipped.
 // Against eight loads and eight weighted adds per voxel and control point this is 4
 // Nv / nz of each, and reads whole cache lines.  180 control points at 128^3 (89-wide
@@ -665,9 +665,9 @@ hipError_t launch_conv_direct(const Geo<T>& g, int nb, const T* z, const T* in, 
 // One control point's terms of a voxel column, its fan reaching the column.
 template <typename T>
 struct GatherCol {
-  T w[4];      // corner (dk, di) = (c >> 1, c & 1): MU x in-grid mask x (1 - wk or wk) x (1 - wi or wi)
+  T w[4];      // corner (dk, di) = (c >> 1, c & 1): in-grid mask x (1 - wk or wk) x (1 - wi or wi)
   int off[4];  // element offset of the corner's row (clamped into the grid)
-  T q;         // SAD / d, which scales z into the lateral coordinate j
+  T q, m;      // SAD / d, which scales z into the lateral coordinate j; MU
   int b;       // control point within the batch
 };
 
@@ -740,7 +740,7 @@ __global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int f
 #pragma unroll
   for (int s = 0; s < ZS; ++s) {
     const int z = z0 + 64 * s;
-    tz[s] = (g.rel_oz + T(z) * g.sz) * g.inv_lat;
+    tz[s] = g.rel_oz + T(z) * g.sz;
     if (!first && z < g.nz) {
       const size_t vox = ((size_t)z * g.ny + y) * g.nx + x;
       sum[s].load(dose[vox], comp[vox]);
@@ -770,6 +770,7 @@ __global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int f
       const int k0 = in_ki ? (int)fk : 0, i0 = in_ki ? (int)fi : 0;
       const T wk = fkv - fk, wi = fiv - fi;
       col.q = q;
+      col.m = m;
       col.b = b;
 #pragma unroll
       for (int dk = 0; dk < 2; ++dk)
@@ -778,7 +779,7 @@ __global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int f
           const int kk = k0 + dk, ii = i0 + di;
           const bool ok = (kk >= 0) & (kk < g.Nk) & (ii >= 0) & (ii < g.Nu);
           const T wkk = dk ? wk : T(1) - wk, wii = di ? wi : T(1) - wi;
-          col.w[2 * dk + di] = ok ? m * (wkk * wii) : T(0);
+          col.w[2 * dk + di] = ok ? wkk * wii : T(0);
           col.off[2 * dk + di] = min(max(kk, 0), g.Nk - 1) * plane + min(max(ii, 0), g.Nu - 1) * g.Nv;
         }
     }
@@ -827,16 +828,16 @@ __global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int f
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int u = 0; u < UU; ++u) {
-        const T q = cols[e0 + u].q;
+        const T q = cols[e0 + u].q, m = cols[e0 + u].m;
         const T* row = rows + u * pitch + GATHER_PAD;
 #pragma unroll
         for (int s = 0; s < ZS; ++s) {
-          const T fjv = tz[s] * q + g.cv;
+          const T fjv = tz[s] * q * g.inv_lat + g.cv;
           const T fj = dfloor(fjv), wj = fjv - fj;
           // outside the plane both words are zero
           const int j = min(max((int)fj, -GATHER_PAD), g.Nv);
           const T lo = row[j], hi = row[j + 1];
-          sum[s].add(lo + wj * (hi - lo));
+          sum[s].add(m * (lo + wj * (hi - lo)));
         }
       }
       __builtin_amdgcn_wave_barrier();

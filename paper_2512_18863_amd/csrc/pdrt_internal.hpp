@@ -46,6 +46,7 @@ struct Geo {
   int fcorr;
   T hs_amp, oar0, oar1;
   int box_du, box_dv;  // pixels by which the corrections widen the aperture rectangle along u and v
+  int conv_du, conv_dv;  // bound of its widening past the field limits by corrections and rotation, each side
   // ray march: 0 = one thread per ray (serial), 1 = segmented scan across wavefronts
   int march_scan;
 };
@@ -134,6 +135,11 @@ hipError_t launch_conv_mfma_f32(const Geo<float>& g, int nb, const float* z, con
 bool conv_fwd_reg_supported(const Geo<float>& g, bool bf16);
 hipError_t launch_conv_fwd_reg(const Geo<float>& g, int nb, const float* z, const float* in, float* out,
                                hipStream_t s, const int* box, bool bf16);
+// adjoint convolution for outputs inside the aperture rectangle (FP32 or BF16
+// operands, h <= 31)
+bool conv_adj_supported(const Geo<float>& g);
+hipError_t launch_conv_adj(const Geo<float>& g, int nb, const float* z, const float* in, float* out, hipStream_t s,
+                           const int* box, bool bf16);
 hipError_t launch_conv_mfma_bf16(const Geo<float>& g, int nb, const float* z, const float* in, float* out,
                                  hipStream_t s, const int* box = nullptr, int support = 0);
 template <typename T>
