@@ -124,10 +124,11 @@ typedef struct {
   double oar[2];
   /* Form of the ray march that evaluates the depth integral of Eq. 7 (the same
    * arithmetic, a different order of the compensated sums, so results agree to
-   * rounding): 0 = one thread per ray walks its planes in order (default, the
-   * faster on the MI355X); 1 = the planes of 64 rays are split over the wavefronts
-   * of a workgroup, each scanning its segment and adding the sums of the segments
-   * before it, exchanged through LDS. */
+   * rounding): 0 = the faster on the MI355X: one thread per ray walks its planes in
+   * order, or, for few rays (by the grid, field limit, kernel size and number of
+   * control points), the scan; 1 = always the scan: the planes of 64 rays are split
+   * over the wavefronts of a workgroup, each scanning its segment and adding the
+   * sums of the segments before it, exchanged through LDS. */
   int32_t march_scan;
 } pdrt_kernel_spec;
 

@@ -217,6 +217,30 @@ int size_problem(const pdrt_grid* grid, const pdrt_beam* beam, const pdrt_kernel
   return PDRT_OK;
 }
 
+// Smallest kernel taken by the FP32 matrix-core convolution: below it the Toeplitz
+// operand is mostly padding (a 9-tap row fills 9 of 32 columns) and the vector-ALU
+// convolutions are faster.
+constexpr int kMfmaMinTaps = 13;
+
+// The segmented scan takes the ray march of problems with few rays, whose serial form
+// is one long dependent chain per ray on an otherwise idle chip.  Wavefronts of rays
+// inside the field limits, ray march and its adjoint in ms, serial / scan: 12 (one
+// field, 183 planes) 0.27 / 0.06, 383 0.28 / 0.12, 765 0.29 / 0.21, 1531 0.37 / 0.37; with
+// more planes than the scan holds at once (318) 420 0.56 / 0.29, 840 0.60 / 0.56, 1681
+// 0.68 / 1.11.  The rule looks only at what a geometry cache is tied to, so that cached
+// and uncached calls march alike; a table too long for the scan's LDS stays serial.
+// Kernels of n <= 11 keep the serial form: their dose
+// feeds the learned correction, whose BF16 layers turn a change of its last bits into
+// one a hundred times larger.
+bool march_few_rays(const pdrt_beam* beam, const pdrt_kernel_spec* spec, const Problem& P, size_t elem) {
+  const int h = (spec->n_taps - 1) / 2;
+  const long bu = std::max(1, P.Nu - 2 * h), bv = std::max(1, P.Nv - 2 * h);
+  const long waves = (bu * bv + 63) / 64 * beam->n_cp;
+  const size_t lds = elem * (2 * kMarchMaxSegments * 64 + (size_t)spec->n_dd);
+  return spec->n_taps >= kMfmaMinTaps && lds <= 64 * 1024 &&
+         waves <= (P.Nk <= kMarchSeg * kMarchMaxSegments ? 1280 : 768);
+}
+
 template <typename T>
 void make_geo(const pdrt_grid* grid, const pdrt_beam* beam, const pdrt_kernel_spec* spec, const Problem& P,
               Geo<T>* g) {
@@ -264,7 +288,7 @@ void make_geo(const pdrt_grid* grid, const pdrt_beam* beam, const pdrt_kernel_sp
   g->hs_amp = (T)spec->hs_amp;
   g->oar0 = (T)spec->oar[0];
   g->oar1 = (T)spec->oar[1];
-  g->march_scan = spec->march_scan;
+  g->march_scan = spec->march_scan || march_few_rays(beam, spec, P, sizeof(T));
 }
 
 // Rectangle sizes the convolutions are shaped for: with collimator angles the field
@@ -301,11 +325,6 @@ void make_fc_taps(const pdrt_kernel_spec* spec, FcTaps<T>* t, Geo<T>* g) {
   } while (0)
 
 #define LAUNCH(name, x) PDRT_TIMED(name, s, x)
-
-// Smallest kernel taken by the FP32 matrix-core convolution: below it the Toeplitz
-// operand is mostly padding (a 9-tap row fills 9 of 32 columns) and the vector-ALU
-// convolutions are faster.
-constexpr int kMfmaMinTaps = 13;
 
 // box / support: the aperture rectangles of the batch and how the convolution may
 // use them (CONV_IN_BOX forward, CONV_OUT_BOX adjoint); kernels without support

@@ -222,7 +222,7 @@ hipError_t launch_ca_depth(const Geo<T>& g, int nb, const T* frame, const T* rho
 // factor G_k = (SAD / d_k)^2 DD(W_k) itself (rounded to E), so that P = F G later.
 enum { MARCH_PRIMARY = 0, MARCH_ADJOINT = 1, MARCH_GEOMETRY = 2 };
 
-// ---- serial form (the default)
+// ---- serial form
 //
 // One thread per divergent ray (i, j) walks its Nk planes in order with a
 // compensated running sum; eight planes' density loads are in flight at a time.
@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(256) k_march_serial(Geo<T> g, const T* __restr
   }
 }
 
-// ---- segmented scan (spec->march_scan)
+// ---- segmented scan (few rays, or spec->march_scan)
 //
 // The inclusive sum as a segmented scan across the wavefronts of a workgroup.
 // The workgroup takes 64 rays (lanes along v, so that neighbouring lanes read
