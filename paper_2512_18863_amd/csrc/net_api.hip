@@ -36,7 +36,7 @@ int pdrt_conv3d_forward(const pdrt_vol* vol, int32_t c1, int32_t c2, const void*
     return PDRT_E_INVALID;
   if ((c1 + c2) % 16 || !(cout == 16 || cout == 32 || cout == 64)) return PDRT_E_UNSUPPORTED;
   PDRT_TIMED("conv3d_fwd", (hipStream_t)stream, launch_conv3d_fwd(V(vol), c1, c2, (const __bf16*)x1, (const __bf16*)x2, cout, (const __bf16*)wt,
-                            kpad(27 * (c1 + c2)), bias, relu, (__bf16*)y, (hipStream_t)stream));
+                            bias, relu, (__bf16*)y, (hipStream_t)stream));
   return PDRT_OK;
 }
 
@@ -49,7 +49,7 @@ int pdrt_conv3d_backward_data(const pdrt_vol* vol, int32_t cout, const void* dy,
   int nt = cin / 16;
   if (cin % 16 || !(nt == 1 || nt == 2 || nt == 3 || nt == 4 || nt == 6)) return PDRT_E_UNSUPPORTED;
   PDRT_TIMED("conv3d_dgrad", (hipStream_t)stream, launch_conv3d_dgrad(V(vol), cout, (const __bf16*)dy, (const __bf16*)y_act, cin, (const __bf16*)wd,
-                              kpad(27 * cout), c1, (__bf16*)dx1, (__bf16*)dx2, (hipStream_t)stream));
+                              c1, (__bf16*)dx1, (__bf16*)dx2, (hipStream_t)stream));
   return PDRT_OK;
 }
 

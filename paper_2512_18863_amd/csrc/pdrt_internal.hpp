@@ -168,9 +168,9 @@ struct Vol {
   int D, H, W;
 };
 hipError_t launch_conv3d_fwd(Vol v, int C1, int C2, const __bf16* X1, const __bf16* X2, int Cout, const __bf16* Wt,
-                             int Kp, const float* bias, int relu, __bf16* Y, hipStream_t s);
+                             const float* bias, int relu, __bf16* Y, hipStream_t s);
 hipError_t launch_conv3d_dgrad(Vol v, int Cout, const __bf16* dY, const __bf16* Yact, int Cin, const __bf16* Wd,
-                               int Kp, int C1, __bf16* dX1, __bf16* dX2, hipStream_t s);
+                               int C1, __bf16* dX1, __bf16* dX2, hipStream_t s);
 bool conv3d_wgrad_mfma_ok(const __bf16* X1, const __bf16* X2, int Cout, const __bf16* dY, const __bf16* Yact);
 int conv3d_wgrad_splits(int Cin, int nsplit);
 hipError_t launch_conv3d_wgrad_mfma(Vol v, int C1, int C2, const __bf16* X1, const __bf16* X2, int Cout,
