@@ -12,6 +12,10 @@ __device__ __forceinline__ float dfloor<float>(float x) { return floorf(x); }
 template <>
 __device__ __forceinline__ double dfloor<double>(double x) { return floor(x); }
 
+// x clamped to [lo, hi] (lo <= hi): one instruction for floats.
+__device__ __forceinline__ float dclamp(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
+__device__ __forceinline__ double dclamp(double x, double lo, double hi) { return fmin(fmax(x, lo), hi); }
+
 template <typename T>
 __device__ __forceinline__ T dexp(T x);
 template <>
@@ -53,61 +57,70 @@ __device__ __forceinline__ T dd_lookup(const T* tab, int n, T inv_step, T W) {
 // Trilinear density sample from the z-fastest copy rho_t [ny][nx][nz] at
 // continuous voxel index (X, Y, Z), zero outside the CT, split in two halves: the
 // fetch issues the eight corner loads from clamped (always valid) addresses, the
-// combine masks and sums them in the order a masked loop would.  A ray march can
-// fetch a few samples ahead, so several samples' loads are in flight together.
+// combine sums them in the order a masked loop would.  A ray march can fetch a few
+// samples ahead, so several samples' loads are in flight together.
+//
+// The ray march is bound by this function's vector instructions, so a corner outside
+// the CT costs none of its own: its x or y weight is zero (the clamped corner holds a
+// finite density), which gives the bits of a masked sum; an index off the CT altogether
+// has both weights of an axis zero; the columns' addresses differ by one of two steps.
+// 152 -> 131 vector instructions a sample of the march, 6 -> 2 integer multiplies; the
+// march of a 180-angle plan at 128^3 0.163 -> 0.147 ms, its adjoint 0.246 -> 0.236.
 template <typename T>
 struct RhoFetch {
   T lo[2][2], hi[2][2];
-  T wx, wy, wz;
-  T m_in, m_z0, m_z1, m_ok[2][2];  // 0/1 masks
+  T wx[2], wy[2], wz;
+  T m_z0, m_z1;  // 0/1 masks
 };
 
 template <typename T>
 __device__ __forceinline__ RhoFetch<T> rho_fetch(const T* __restrict__ rho_t, int nx, int ny, int nz, T X, T Y, T Z) {
   RhoFetch<T> r;
-  const T fx0 = dfloor(X), fy0 = dfloor(Y), fz0 = dfloor(Z);
-  // (bitwise & keeps the flags branch free)
-  const bool inside = (fx0 >= T(-1)) & (fx0 < T(nx)) & (fy0 >= T(-1)) & (fy0 < T(ny)) & (fz0 >= T(-1)) &
-                      (fz0 < T(nz));
-  const int x0 = inside ? (int)fx0 : 0, y0 = inside ? (int)fy0 : 0, z0 = inside ? (int)fz0 : 0;
-  r.wx = X - fx0;
-  r.wy = Y - fy0;
-  r.wz = Z - fz0;
-  r.m_in = T(inside);
-  r.m_z0 = T(z0 >= 0);
-  r.m_z1 = T(z0 + 1 < nz);
-  const int za = max(z0, 0), zb = min(z0 + 1, nz - 1);
+  // (clamped to where both corners are outside, so that the conversions are defined)
+  const T Xc = dclamp(X, T(-2), T(nx)), Yc = dclamp(Y, T(-2), T(ny)), Zc = dclamp(Z, T(-2), T(nz));
+  const T fx0 = dfloor(Xc), fy0 = dfloor(Yc), fz0 = dfloor(Zc);
+  const int x0 = (int)fx0, y0 = (int)fy0, z0 = (int)fz0;
+  const T wx = Xc - fx0, wy = Yc - fy0;
+  r.wx[0] = (unsigned)x0 < (unsigned)nx ? T(1) - wx : T(0);
+  r.wx[1] = (unsigned)(x0 + 1) < (unsigned)nx ? wx : T(0);
+  r.wy[0] = (unsigned)y0 < (unsigned)ny ? T(1) - wy : T(0);
+  r.wy[1] = (unsigned)(y0 + 1) < (unsigned)ny ? wy : T(0);
+  r.wz = Zc - fz0;
+  r.m_z0 = (unsigned)z0 < (unsigned)nz ? T(1) : T(0);
+  r.m_z1 = (unsigned)(z0 + 1) < (unsigned)nz ? T(1) : T(0);
+  const int cx = min(max(x0, 0), nx - 1), cy = min(max(y0, 0), ny - 1);
+  const int za = min(max(z0, 0), nz - 1), zb = min(max(z0 + 1, 0), nz - 1);
+  // (the volume holds fewer than 2^31 voxels; unsigned, so that no index is sign-extended)
+  const unsigned c00 = (unsigned)(cy * nx + cx) * nz;
+  const unsigned c01 = c00 + ((unsigned)x0 < (unsigned)(nx - 1) ? nz : 0);
+  const unsigned dy = (unsigned)y0 < (unsigned)(ny - 1) ? nx * nz : 0;
+  const unsigned col[2][2] = {{c00, c01}, {c00 + dy, c01 + dy}};
 #pragma unroll
-  for (int dy = 0; dy < 2; ++dy)
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int dx = 0; dx < 2; ++dx) {
-      const int y = y0 + dy, x = x0 + dx;
-      r.m_ok[dy][dx] = T((y >= 0) & (y < ny) & (x >= 0) & (x < nx));
-      const int cy = min(max(y, 0), ny - 1), cx = min(max(x, 0), nx - 1);
-      const T* col = rho_t + (cy * nx + cx) * nz;  // (the volume holds fewer than 2^31 voxels)
-      r.lo[dy][dx] = col[za];
-      r.hi[dy][dx] = col[zb];
+    for (int i = 0; i < 2; ++i) {
+      r.lo[j][i] = rho_t[col[j][i] + za];
+      r.hi[j][i] = rho_t[col[j][i] + zb];
     }
   return r;
 }
 
-// Masks are 0/1 factors rather than selects (the clamped corners hold finite
-// densities), so the compiler has no reason to make the loads conditional.
 template <typename T>
 __device__ __forceinline__ T rho_combine(const RhoFetch<T>& r) {
   T s = T(0);
 #pragma unroll
-  for (int dy = 0; dy < 2; ++dy) {
-    const T wyv = dy ? r.wy : T(1) - r.wy;
+  for (int dy = 0; dy < 2; ++dy)
 #pragma unroll
     for (int dx = 0; dx < 2; ++dx) {
-      const T wxv = dx ? r.wx : T(1) - r.wx;
       const T a = r.m_z0 * r.lo[dy][dx];
       const T b = r.m_z1 * r.hi[dy][dx];
-      s += r.m_ok[dy][dx] * (wyv * wxv * (a + r.wz * (b - a)));
+      const T t = r.wy[dy] * r.wx[dx] * (a + r.wz * (b - a));
+      {
+#pragma clang fp contract(off)
+        s = s + t;  // (the product rounded by itself, as a masked sum has it)
+      }
     }
-  }
-  return r.m_in * s;
+  return s;
 }
 
 template <typename T>

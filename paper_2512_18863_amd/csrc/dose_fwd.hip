@@ -184,7 +184,7 @@ __global__ void __launch_bounds__(64) k_ca_depth(Geo<T> g, const T* __restrict__
   int b = blockIdx.x;
   int lane = threadIdx.x;
   T sn = frame[2 * b], cs = frame[2 * b + 1];
-  T carry = T(0);
+  T carry = T(0) * (sn + cs);  // (an angle that is NaN leaves a NaN depth)
   for (int k0 = 0; k0 < g.Nk; k0 += 64) {
     int k = k0 + lane;
     T val = T(0);
@@ -253,7 +253,7 @@ __device__ __forceinline__ void march_ray(const Geo<T>& g, int b, int i, int j, 
   T ucs = u * cs, usn = u * sn;
   T ds = g.dstep * dsqrt(T(1) + (u * u + v * v) * (g.inv_sad * g.inv_sad));
   const T* zb = zca + (size_t)b * g.Nk;
-  T W = T(0), c = T(0), acc = T(0);
+  T W = T(0) * (sn + cs), c = T(0), acc = T(0);  // (an angle that is NaN leaves a NaN depth)
   // one step of the march: the water-equivalent depth Wk of plane k, then the
   // primary (or its adjoint, or the factor itself) at that plane
   auto step = [&](int k, T Wk) {
@@ -415,7 +415,7 @@ __global__ void __launch_bounds__(64 * MARCH_MAXW) k_march_scan(Geo<T> g, const 
     }
     __syncthreads();
     // carry: the sums of the segments before this one, in plane order
-    T W = T(0), cW = T(0);
+    T W = T(0) * (sn + cs), cW = T(0);  // (an angle that is NaN leaves a NaN depth)
     if (per_ray)
       for (int w2 = 0; w2 < w; ++w2) kahan_add(W, cW, seg[w2 * 64 + lane] - seg[(MARCH_MAXW + w2) * 64 + lane]);
     T Fv = T(1);
