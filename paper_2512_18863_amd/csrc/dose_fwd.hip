@@ -759,10 +759,11 @@ __global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int f
     if (b < nb) {
       const T sn = frame[2 * b], cs = frame[2 * b + 1], m = mu[b];
       bad |= !(m - m == T(0));
-      // voxel_to_fan without the z part
-      const T ev = -sn * tx + cs * ty;
+      // voxel_to_fan without the z part (the fused products spelt out: the learned
+      // correction's BF16 layers turn a dose's last bits into differences of 2.5e-5)
+      const T ev = fma(cs, ty, -sn * tx);
       const T q = T(1) / (T(1) + ev * g.inv_sad);
-      const T u = (cs * tx + sn * ty) * q;
+      const T u = fma(cs, tx, sn * ty) * q;
       const T fkv = (ev - g.e0) * g.inv_dstep, fiv = u * g.inv_lat + g.cu;
       const T fk = dfloor(fkv), fi = dfloor(fiv);
       const bool in_ki = (fk >= T(-1)) & (fk < T(g.Nk)) & (fi >= T(-1)) & (fi < T(g.Nu));
