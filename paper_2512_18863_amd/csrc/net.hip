@@ -210,16 +210,39 @@ __global__ void k_up2_bwd(Vol v, int C, const __bf16* __restrict__ dY, __bf16* _
 // channel (a residual on the small-kernel dose), output 1 the error estimate.
 //   pred[p] = dose[p] * scale + hb[0] + sum_c hw[0][c] X[p][c]
 //   resid[p] = hb[1] + sum_c hw[1][c] X[p][c]
+//
+// Positions are C channels apart, so channels are moved eight (16 bytes) at a time
+// (WIDE: C a multiple of 8, 16-byte aligned; else one by one); read singly a wavefront's
+// 2-byte loads touched every line eight times: 0.067 ms at 128^3 with 16 channels, 0.020 now.
+template <bool WIDE>
+__device__ __forceinline__ void load_channels(const __bf16* __restrict__ X, size_t at, int n, float (&x)[8]) {
+  if (WIDE) {
+    const nbf16x8 v = *reinterpret_cast<const nbf16x8*>(X + at);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = (float)v[e];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = e < n ? (float)X[at + e] : 0.f;
+  }
+}
+
+template <bool WIDE>
 __global__ void k_head(int P, int C, const __bf16* __restrict__ X, const float* __restrict__ hw,
                        const float* __restrict__ hb, const float* __restrict__ dose, const float* __restrict__ scale,
                        float* __restrict__ pred, float* __restrict__ resid) {
   int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= P) return;
   float a = hb[0], r = hb[1];
-  for (int c = 0; c < C; ++c) {
-    float x = (float)X[(size_t)p * C + c];
-    a += hw[c] * x;
-    r += hw[C + c] * x;
+  for (int c0 = 0; c0 < C; c0 += 8) {
+    float x[8];
+    load_channels<WIDE>(X, (size_t)p * C + c0, C - c0, x);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if (WIDE || c0 + e < C) {
+        a += hw[c0 + e] * x[e];
+        r += hw[C + c0 + e] * x[e];
+      }
+    }
   }
   pred[p] = dose[p] * scale[0] + a;
   resid[p] = r;
@@ -227,39 +250,67 @@ __global__ void k_head(int P, int C, const __bf16* __restrict__ X, const float* 
 
 // Backward of the head for upstream gradients gp (pred) and gr (resid):
 //   dX[p][c] = gp hw[0][c] + gr hw[1][c];  per-block partials of dhw, dhb.
+// The partials of eight channels are put side by side in LDS and summed by the
+// wavefronts, a value each at a time, in the order of a tree over the block's 256
+// positions (t + (t + 128), then + 64, ... 1): two barriers for 16 sums where a tree per
+// value took nine each, 0.201 -> 0.044 ms at 128^3 (0.081 -> 0.018 without partials).
+template <bool WIDE>
 __global__ void __launch_bounds__(256) k_head_bwd(int P, int C, const __bf16* __restrict__ X,
                                                   const float* __restrict__ hw, const float* __restrict__ gp,
                                                   const float* __restrict__ gr, __bf16* __restrict__ dX,
                                                   float* __restrict__ part) {
-  __shared__ float red[256];
-  int p = blockIdx.x * 256 + threadIdx.x;
+  __shared__ float red[16][256];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int p = blockIdx.x * 256 + t, np = 2 * C + 2;
   float g0 = 0.f, g1 = 0.f;
   if (p < P) {
     g0 = gp[p];
     g1 = gr ? gr[p] : 0.f;
   }
-  const int np = part ? 2 * C + 2 : 0;  // no head-weight gradient wanted: skip the partial sums
-  for (int j = 0; j < np; ++j) {
-    float v = 0.f;
+  // the sums of red[0 .. n), value i to place at(i)
+  auto sums = [&](int n, auto at) {
+    __syncthreads();
+    for (int i = wave; i < n; i += 4) {
+      float v = (red[i][lane] + red[i][lane + 128]) + (red[i][lane + 64] + red[i][lane + 192]);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+      const int j = at(i);
+      if (lane == 0 && j >= 0) part[(size_t)blockIdx.x * np + j] = v;
+    }
+    __syncthreads();
+  };
+  for (int c0 = 0; c0 < C; c0 += 8) {
+    if (part) {  // (no head-weight gradient wanted: the partial sums are skipped)
+      float x[8] = {};
+      if (p < P) load_channels<WIDE>(X, (size_t)p * C + c0, C - c0, x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        red[e][t] = p < P ? g0 * x[e] : 0.f;
+        red[8 + e][t] = p < P ? g1 * x[e] : 0.f;
+      }
+      sums(16, [&](int i) { return c0 + (i & 7) < C ? (i >> 3) * C + c0 + (i & 7) : -1; });
+    }
     if (p < P) {
-      if (j < 2 * C) {
-        int o = j / C, c = j - o * C;
-        v = (o ? g1 : g0) * (float)X[(size_t)p * C + c];
+      nbf16x8 d;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int c = min(c0 + e, C - 1);
+        d[e] = (__bf16)(g0 * hw[c] + g1 * hw[C + c]);
+      }
+      if (WIDE) {
+        *reinterpret_cast<nbf16x8*>(dX + (size_t)p * C + c0) = d;
       } else {
-        v = (j == 2 * C) ? g0 : g1;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (c0 + e < C) dX[(size_t)p * C + c0 + e] = d[e];
       }
     }
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-      if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) part[(size_t)blockIdx.x * np + j] = red[0];
-    __syncthreads();
   }
-  if (p < P)
-    for (int c = 0; c < C; ++c) dX[(size_t)p * C + c] = (__bf16)(g0 * hw[c] + g1 * hw[C + c]);
+  if (part) {
+    red[0][t] = g0;
+    red[1][t] = g1;
+    sums(2, [&](int i) { return 2 * C + i; });
+  }
 }
 
 // Training loss over a mask: L = sum_p m [(pred - T)^2 + lam (resid - |pred - T|)^2] / sum m,
@@ -527,13 +578,17 @@ hipError_t launch_up2(Vol v, int C, const __bf16* X, __bf16* Y, int backward, hi
 
 hipError_t launch_head(int P, int C, const __bf16* X, const float* hw, const float* hb, const float* dose,
                        const float* scale, float* pred, float* resid, hipStream_t s) {
-  hipLaunchKernelGGL(k_head, dim3(nblk(P)), dim3(256), 0, s, P, C, X, hw, hb, dose, scale, pred, resid);
+  const bool wide = C % 8 == 0 && ((uintptr_t)X & 15) == 0;
+  hipLaunchKernelGGL(wide ? k_head<true> : k_head<false>, dim3(nblk(P)), dim3(256), 0, s, P, C, X, hw, hb, dose, scale,
+                     pred, resid);
   return hipGetLastError();
 }
 
 hipError_t launch_head_bwd(int P, int C, const __bf16* X, const float* hw, const float* gp, const float* gr,
                            __bf16* dX, float* part, hipStream_t s) {
-  hipLaunchKernelGGL(k_head_bwd, dim3(nblk(P)), dim3(256), 0, s, P, C, X, hw, gp, gr, dX, part);
+  const bool wide = C % 8 == 0 && (((uintptr_t)X | (uintptr_t)dX) & 15) == 0;
+  hipLaunchKernelGGL(wide ? k_head_bwd<true> : k_head_bwd<false>, dim3(nblk(P)), dim3(256), 0, s, P, C, X, hw, gp, gr,
+                     dX, part);
   return hipGetLastError();
 }
 
