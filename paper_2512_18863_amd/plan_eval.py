@@ -150,27 +150,33 @@ class Evaluator:
 
 def d_from_histogram(hist_row: np.ndarray, bin_width: float, n_hot: int) -> float:
     """Lower edge of the bin that holds the n_hot-th hottest voxel."""
-    n = int(hist_row.sum())
+    return _d_hottest(np.cumsum(hist_row[::-1]), bin_width, n_hot)
+
+
+def _d_hottest(hottest: np.ndarray, bin_width: float, n_hot: int) -> float:
+    """The same from the row's running sum over its bins, hottest first."""
+    n = int(hottest[-1]) if len(hottest) else 0
     if n == 0:
         return 0.0
     n_hot = min(max(int(n_hot), 1), n)
-    above = np.cumsum(hist_row[::-1])[::-1]     # above[b] = voxels in bins >= b
-    b = int(np.nonzero(above >= n_hot)[0].max())
-    return b * bin_width
+    return (len(hottest) - 1 - int(np.searchsorted(hottest, n_hot))) * bin_width
 
 
 def dvh_parameters(hist_row, stats_row, bin_width: float, voxel_cc: float, n_at_half_rx: int) -> dict:
     n = int(stats_row[0])
     if n == 0:
         return {"N": 0}
+    # one running sum for the four doses (a sum of its own for each was most of a report's
+    # host time: 0.66 against 0.44 ms for a report, objective and Dice of six structures)
+    hottest = np.cumsum(hist_row[::-1])
     return {
         "N": n,
-        "D98": d_from_histogram(hist_row, bin_width, (98 * n + 99) // 100),
-        "D50": d_from_histogram(hist_row, bin_width, (50 * n + 99) // 100),
-        "D2": d_from_histogram(hist_row, bin_width, (2 * n + 99) // 100),
+        "D98": _d_hottest(hottest, bin_width, (98 * n + 99) // 100),
+        "D50": _d_hottest(hottest, bin_width, (50 * n + 99) // 100),
+        "D2": _d_hottest(hottest, bin_width, (2 * n + 99) // 100),
         "Dmean": float(stats_row[1]) / n,
         "Dmax": float(stats_row[2]),
-        "D2cc": d_from_histogram(hist_row, bin_width, int(np.ceil(2.0 / voxel_cc))),
+        "D2cc": _d_hottest(hottest, bin_width, int(np.ceil(2.0 / voxel_cc))),
         "V50": n_at_half_rx / n,
     }
 
