@@ -36,21 +36,22 @@ _CONV = ["conv_mfma.hip", "conv_common.hpp", "taps.hpp", "device_math.hpp", "pdr
 _CONV16 = ["conv_bf16.hip", "conv_common.hpp", "taps.hpp", "device_math.hpp", "pdrt_internal.hpp"]
 _FWDREG = ["conv_fwd_reg.hip", "conv_mfma.hip", "conv_bf16.hip", "conv_common.hpp", "taps.hpp", "device_math.hpp",
            "pdrt_internal.hpp"]
+_ADJ = ["conv_adj.hip"] + _CONV
 _FWD = ["dose_fwd.hip", "taps.hpp", "device_math.hpp", "pdrt_internal.hpp"]
 _BWD = ["dose_bwd.hip", "device_math.hpp", "pdrt_internal.hpp"]
 KERNELS = {
-    # forwards: the register-resident kernel <BF16?, T, SU>
-    "conv_mfma_f32": (("k_conv_fwd_reg<false,",), _FWDREG),
-    # adjoint: the window kernel <NW, TPW> (the region kernel serves the fluence corrections)
-    "conv_mfma_f32_adj": (("k_conv_f32_adj_win<", "k_conv_mfma_f32_adj<"), _CONV),
-    "conv_mfma_bf16": (("k_conv_fwd_reg<true,",), _FWDREG),
-    # BF16 adjoint: the window kernel <NK> (the tiled kernel <NK, BR, BC, NWB, NWP, SUP> with
-    # 2 x 2 tiles in four wavefronts serves the fluence corrections)
-    "conv_mfma_bf16_adj": (("k_conv_bf16_adj_win<", "k_conv_bf16<*,2,2,1,4,*"), _CONV16),
+    # forwards: the register-resident kernel <pieces, T, SU>
+    "conv_mfma_f32": (("k_conv_fwd_reg<3,",), _FWDREG),
+    # adjoint: <pieces, T, CB>
+    "conv_mfma_f32_adj": (("k_conv_adj<3,",), _ADJ),
+    "conv_mfma_bf16": (("k_conv_fwd_reg<1,",), _FWDREG),
+    # BF16 adjoint: the window kernel <NK> (k_conv_adj<1, ...> serves wider rectangles and
+    # the fluence corrections)
+    "conv_mfma_bf16_adj": (("k_conv_bf16_adj_win<", "k_conv_adj<1,"), _CONV16 + ["conv_adj.hip"]),
     "march": (("k_march_serial<float,0,",), _FWD),
     "march_adj": (("k_march_serial<float,1,",), _FWD),
     "gather": (("k_gather<float",), _FWD),
-    "backproject_adj": (("k_backproject_reg<float", "k_backproject_adj<float"), _BWD),
+    "backproject_adj": (("k_backproject_lds<", "k_backproject_reg<float", "k_backproject_adj<float"), _BWD),
 }
 
 
