@@ -652,6 +652,11 @@ hipError_t launch_conv_direct(const Geo<T>& g, int nb, const T* z, const T* in, 
 // planes, 1.04 GB of Dfan): 0.41 ms (2.6 TB/s; eight loads per voxel: 0.92 ms); 90 at
 // 128 x 128 x 96 (43-wide): 0.084 ms (0.33).  Latency of the loads bounds it.
 //
+// A column's z reach a window of the row only, nz s_z / lat pixels at the axis.  Where
+// that takes fewer 64-wide pieces than the plane (thin grids under wide planes) the
+// wavefront loads and blends the window alone (WIN): 60 control points, 16 slices of
+// 224 x 224 under 191-wide planes 0.30 ms (whole rows 0.82, eight loads per voxel 0.40).
+//
 // The terms are summed in control-point order, in FP64 for the FP32 path (an exact
 // sum of FP32 terms to 53 bits, two instructions a term where the compensated FP32
 // sum takes seven) and with Neumaier compensation for the FP64 path; across batches
@@ -669,6 +674,7 @@ struct GatherCol {
   int off[4];  // element offset of the corner's row (clamped into the grid)
   T q, m;      // SAD / d, which scales z into the lateral coordinate j; MU
   int b;       // control point within the batch
+  int jb;      // first pixel of the window (WIN)
 };
 
 constexpr int GATHER_CHUNK = 64;  // control points examined at once, one per lane
@@ -710,10 +716,10 @@ struct GatherSum<double> {
   __device__ double value(double calib) const { return calib * (s + c); }
 };
 
-// JS: ceil(Nv / 64), or 0 for a loop over wider planes; ZS: z per lane; PX x PY: the
-// block's patch of columns; U: control points in flight.
-template <typename T, int JS, int ZS, int PX, int PY, int U>
-__global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int first, int last, int zc, int xc, int yc,
+// JS: ceil(Nv / 64), or 0 for a loop over wider planes, or (WIN) the 64-wide pieces of the
+// window; ZS: z per lane; PX x PY: the block's patch of columns; U: control points in flight.
+template <typename T, int JS, int ZS, int PX, int PY, int U, bool WIN>
+__global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int first, int last, int win, int zc, int xc, int yc,
                                                          const T* __restrict__ frame, const T* __restrict__ mu,
                                                          const T* __restrict__ Dfan, T* __restrict__ dose,
                                                          T* __restrict__ comp) {
@@ -773,6 +779,11 @@ __global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int f
       col.q = q;
       col.m = m;
       col.b = b;
+      if constexpr (WIN) {
+        // one pixel before the first z's, for rounding; from the zero beside the plane on
+        const T fj = dfloor((g.rel_oz + T(zq * 64 * ZS) * g.sz) * q * g.inv_lat + g.cv);
+        col.jb = min(max((int)fj - 1, -1), g.Nv);
+      }
 #pragma unroll
       for (int dk = 0; dk < 2; ++dk)
 #pragma unroll
@@ -802,7 +813,11 @@ __global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int f
           for (int cc = 0; cc < 4; ++cc) {
             const T* row = base + uniform(c.off[cc]);
 #pragma unroll
-            for (int s = 0; s < JS; ++s) v[u][s][cc] = row[(unsigned)min(64 * s + lane, g.Nv - 1)];
+            for (int s = 0; s < JS; ++s) {
+              // (lanes past the window read its last pixel again)
+              const int j = WIN ? max(uniform(c.jb) + min(64 * s + lane, win - 1), 0) : 64 * s + lane;
+              v[u][s][cc] = row[(unsigned)min(j, g.Nv - 1)];
+            }
           }
         }
 #pragma unroll
@@ -813,7 +828,12 @@ __global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int f
             T r = T(0);
 #pragma unroll
             for (int cc = 0; cc < 4; ++cc) r += c.w[cc] * v[u][s][cc];
-            if (64 * s + lane < g.Nv) rows[u * pitch + GATHER_PAD + 64 * s + lane] = r;
+            if constexpr (WIN) {
+              const int j = uniform(c.jb) + 64 * s + lane;
+              rows[u * pitch + GATHER_PAD + 64 * s + lane] = j >= 0 && j < g.Nv ? r : T(0);
+            } else if (64 * s + lane < g.Nv) {
+              rows[u * pitch + GATHER_PAD + 64 * s + lane] = r;
+            }
           }
         }
       } else {
@@ -836,7 +856,8 @@ __global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int f
           const T fjv = tz[s] * q * g.inv_lat + g.cv;
           const T fj = dfloor(fjv), wj = fjv - fj;
           // outside the plane both words are zero
-          const int j = min(max((int)fj, -GATHER_PAD), g.Nv);
+          int j = min(max((int)fj, -GATHER_PAD), g.Nv);
+          if constexpr (WIN) j = min(max(j - uniform(cols[e0 + u].jb), -GATHER_PAD), 64 * JS);
           const T lo = row[j], hi = row[j + 1];
           sum[s].add(m * (lo + wj * (hi - lo)));
         }
@@ -862,8 +883,8 @@ __global__ void __launch_bounds__(64 * PX * PY) k_gather(Geo<T> g, int nb, int f
   }
 }
 
-template <typename T, int JS, int ZS>
-static hipError_t launch_gather_cfg(const Geo<T>& g, int nb, int first, int last, const T* frame, const T* mu,
+template <typename T, int JS, int ZS, bool WIN>
+static hipError_t launch_gather_cfg(const Geo<T>& g, int nb, int first, int last, int win, const T* frame, const T* mu,
                                     const T* Dfan, T* dose, T* comp, hipStream_t s) {
   // Two control points in flight: four need more registers and lose more to the lower
   // occupancy than they hide (128^3: 0.58 ms against 0.43); one: 0.40, but 0.11 against
@@ -876,34 +897,58 @@ static hipError_t launch_gather_cfg(const Geo<T>& g, int nb, int first, int last
   const int js = JS ? JS : (g.Nv + 63) / 64;
   const size_t lds = (size_t)PX * PY * (GATHER_CHUNK * sizeof(GatherCol<T>) + U * (64 * js + 2 * GATHER_PAD) * sizeof(T));
   if (lds > 160 * 1024) return hipErrorInvalidConfiguration;
-  const void* kern = (const void*)k_gather<T, JS, ZS, PX, PY, U>;
+  const void* kern = (const void*)k_gather<T, JS, ZS, PX, PY, U, WIN>;
   {
     hipError_t e = ensure_lds_limit(kern, (int)lds);
     if (e != hipSuccess) return e;
   }
   const int grid = (int)((nblk + 7) / 8 * 8);
-  hipLaunchKernelGGL((k_gather<T, JS, ZS, PX, PY, U>), dim3(grid), dim3(64 * PX * PY), lds, s, g, nb, first, last, zc,
-                     xc, yc, frame, mu, Dfan, dose, comp);
+  hipLaunchKernelGGL((k_gather<T, JS, ZS, PX, PY, U, WIN>), dim3(grid), dim3(64 * PX * PY), lds, s, g, nb, first, last,
+                     win, zc, xc, yc, frame, mu, Dfan, dose, comp);
   return hipGetLastError();
 }
 
-template <typename T, int JS>
-static hipError_t launch_gather_js(const Geo<T>& g, int nb, int first, int last, const T* frame, const T* mu,
+template <typename T, int JS, bool WIN>
+static hipError_t launch_gather_js(const Geo<T>& g, int nb, int first, int last, int win, const T* frame, const T* mu,
                                    const T* Dfan, T* dose, T* comp, hipStream_t s) {
-  if (g.nz <= 64) return launch_gather_cfg<T, JS, 1>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
-  if (g.nz <= 128) return launch_gather_cfg<T, JS, 2>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
-  return launch_gather_cfg<T, JS, 3>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
+  if (g.nz <= 64) return launch_gather_cfg<T, JS, 1, WIN>(g, nb, first, last, win, frame, mu, Dfan, dose, comp, s);
+  if (g.nz <= 128) return launch_gather_cfg<T, JS, 2, WIN>(g, nb, first, last, win, frame, mu, Dfan, dose, comp, s);
+  return launch_gather_cfg<T, JS, 3, WIN>(g, nb, first, last, win, frame, mu, Dfan, dose, comp, s);
+}
+
+// Pixels of the window that a wavefront's z reach, largest next to the source
+// (columns reached lie at most a plane outside the planes): the step between the first
+// and last z, a pixel at each end for the cells' two sides and one for rounding.
+template <typename T>
+static int gather_window(const Geo<T>& g) {
+  const double d = 1.0 + ((double)g.e0 - (double)g.dstep) * (double)g.inv_sad;  // SAD / d at its largest
+  if (!(d > 1e-3)) return 1 << 20;
+  const int nzw = min(g.nz, g.nz <= 64 ? 64 : g.nz <= 128 ? 128 : 192);
+  const double span = (double)(nzw - 1) * (double)g.sz * (double)g.inv_lat / d * (1.0 + 1e-5);
+  return span < 1e6 ? (int)span + 6 : 1 << 20;
 }
 
 template <typename T>
 hipError_t launch_gather(const Geo<T>& g, int nb, int first, int last, const T* frame, const T* mu, const T* Dfan,
                          T* dose, T* comp, hipStream_t s) {
   if ((long)g.Nk * g.Nu * g.Nv > 0x7fffffffL) return hipErrorInvalidConfiguration;  // 32-bit corner offsets
-  if (g.Nv <= 64) return launch_gather_js<T, 1>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
-  if (g.Nv <= 128) return launch_gather_js<T, 2>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
-  if (g.Nv <= 192) return launch_gather_js<T, 3>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
-  if (g.Nv <= 256) return launch_gather_js<T, 4>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
-  return launch_gather_js<T, 0>(g, nb, first, last, frame, mu, Dfan, dose, comp, s);
+  const int js = (g.Nv + 63) / 64, win = gather_window(g);
+  if ((win + 63) / 64 < js) {
+    switch ((win + 63) / 64) {
+      case 1: return launch_gather_js<T, 1, true>(g, nb, first, last, win, frame, mu, Dfan, dose, comp, s);
+      case 2: return launch_gather_js<T, 2, true>(g, nb, first, last, win, frame, mu, Dfan, dose, comp, s);
+      case 3: return launch_gather_js<T, 3, true>(g, nb, first, last, win, frame, mu, Dfan, dose, comp, s);
+      case 4: return launch_gather_js<T, 4, true>(g, nb, first, last, win, frame, mu, Dfan, dose, comp, s);
+      default: break;
+    }
+  }
+  switch (js) {
+    case 1: return launch_gather_js<T, 1, false>(g, nb, first, last, 0, frame, mu, Dfan, dose, comp, s);
+    case 2: return launch_gather_js<T, 2, false>(g, nb, first, last, 0, frame, mu, Dfan, dose, comp, s);
+    case 3: return launch_gather_js<T, 3, false>(g, nb, first, last, 0, frame, mu, Dfan, dose, comp, s);
+    case 4: return launch_gather_js<T, 4, false>(g, nb, first, last, 0, frame, mu, Dfan, dose, comp, s);
+    default: return launch_gather_js<T, 0, false>(g, nb, first, last, 0, frame, mu, Dfan, dose, comp, s);
+  }
 }
 
 #define PDRT_INST(T)                                                                                         \
