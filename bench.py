@@ -244,7 +244,7 @@ def per_step(kernels, steps):
     return {k: round(v[1] / steps, 4) for k, v in sorted(kernels.items())}
 
 
-def run_gpu(case, conv, steps, warmup, w, cache=None, forward_only=False, march_scan=False):
+def run_gpu(case, conv, steps, warmup, w, cache=None, forward_only=False, march_scan=None):
     """Forward + backward (or forward only) timed over `steps`; with cache = "fp32" /
     "bf16" the plan's geometry cache is built first (once per plan, not timed)."""
     import torch
@@ -591,8 +591,8 @@ def main():
     rs = run_gpu(case, "fp32", K, W, w, march_scan=True)
     variants["fp32_march_scan"] = {
         "value": round(n_cp / (rs["median_ms"] / 1e3), 3), "ms_per_step": round(rs["median_ms"], 4),
-        "march": "depth integral as a segmented scan over the wavefronts of a workgroup (spec.march_scan = 1); "
-                 "the default is one thread per ray",
+        "march": "depth integral as a segmented scan over the wavefronts of a workgroup (march_scan=True); "
+                 "the default takes one thread per ray at this number of rays",
         "max_abs_err_vs_default_over_max": float(np.abs(rs["dose"].astype(np.float64) - d32).max()
                                                  / np.abs(d32).max()),
         "roofline_kernels": {k: roofline_entry(k, rs["kernels"], K, work) for k in ("march", "march_adj")},

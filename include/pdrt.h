@@ -54,6 +54,10 @@ extern "C" {
 #define PDRT_CONV_FP32 0 /* lateral convolution in FP32 */
 #define PDRT_CONV_BF16 1 /* lateral convolution with BF16 operands, FP32 accumulation */
 
+#define PDRT_MARCH_SERIAL 0 /* ray march: one thread per ray */
+#define PDRT_MARCH_SCAN 1   /* ray march: segmented scan over the wavefronts of a workgroup */
+#define PDRT_MARCH_AUTO 2   /* the faster of the two for the problem */
+
 #define PDRT_CACHE_F32 0  /* geometry cache holds G in FP32: results identical to the uncached path */
 #define PDRT_CACHE_BF16 1 /* geometry cache holds G in BF16 (half the bytes, G rounded to 8 bits) */
 
@@ -124,11 +128,14 @@ typedef struct {
   double oar[2];
   /* Form of the ray march that evaluates the depth integral of Eq. 7 (the same
    * arithmetic, a different order of the compensated sums, so results agree to
-   * rounding): 0 = the faster on the MI355X: one thread per ray walks its planes in
-   * order, or, for few rays (by the grid, field limit, kernel size and number of
-   * control points), the scan; 1 = always the scan: the planes of 64 rays are split
-   * over the wavefronts of a workgroup, each scanning its segment and adding the
-   * sums of the segments before it, exchanged through LDS. */
+   * rounding): PDRT_MARCH_SERIAL = one thread per ray walks its planes in order;
+   * PDRT_MARCH_SCAN = the planes of 64 rays are split over the wavefronts of a
+   * workgroup, each scanning its segment and adding the sums of the segments before
+   * it, exchanged through LDS; PDRT_MARCH_AUTO = the scan's sums for few rays (by the
+   * grid, field limit, number of control points, kernel size, depth-dose table length
+   * and element size), else the serial ones.  A dose under AUTO can therefore change
+   * in its last bits with the number of control points in the beam; kernels of at most
+   * 11 taps always march serially under it. */
   int32_t march_scan;
 } pdrt_kernel_spec;
 

@@ -112,7 +112,7 @@ int validate(const pdrt_grid* grid, const pdrt_beam* beam, const pdrt_kernel_spe
       if (!std::isfinite(spec->kpoly[a][b])) return PDRT_E_INVALID;
   if (!(spec->kz_max_mm >= 0.0) || !std::isfinite(spec->kz_max_mm)) return PDRT_E_INVALID;
   if (spec->max_cp_batch < 0) return PDRT_E_INVALID;
-  if (spec->march_scan != 0 && spec->march_scan != 1) return PDRT_E_INVALID;
+  if (spec->march_scan < PDRT_MARCH_SERIAL || spec->march_scan > PDRT_MARCH_AUTO) return PDRT_E_INVALID;
   if (spec->fluence_corr != 0 && spec->fluence_corr != 1) return PDRT_E_INVALID;
   if (spec->fluence_corr) {
     const double sig[3] = {spec->pen_fwhm_mm[0] / kFwhmPerSigma, spec->pen_fwhm_mm[1] / kFwhmPerSigma,
@@ -222,16 +222,17 @@ int size_problem(const pdrt_grid* grid, const pdrt_beam* beam, const pdrt_kernel
 // convolutions are faster.
 constexpr int kMfmaMinTaps = 13;
 
-// The segmented scan takes the ray march of problems with few rays, whose serial form
+// PDRT_MARCH_AUTO: the segmented scan takes the ray march of problems with few rays, whose serial form
 // is one long dependent chain per ray on an otherwise idle chip.  Wavefronts of rays
 // inside the field limits, ray march and its adjoint in ms, serial / scan: 12 (one
 // field, 183 planes) 0.27 / 0.06, 383 0.28 / 0.12, 765 0.29 / 0.21, 1531 0.37 / 0.37; with
 // more planes than the scan holds at once (318) 420 0.56 / 0.29, 840 0.60 / 0.56, 1681
 // 0.68 / 1.11.  The rule looks only at what a geometry cache is tied to, so that cached
 // and uncached calls march alike; a table too long for the scan's LDS stays serial.
-// Kernels of n <= 11 keep the serial form: their dose
-// feeds the learned correction, whose BF16 layers turn a change of its last bits into
-// one a hundred times larger.
+// Kernels of n <= 11 keep the serial form: theirs are the doses that the learned
+// correction is trained on and reads, and its BF16 layers turn a change of their last
+// bits into one a hundred times larger (the correction's own engines ask for the serial
+// form whatever the kernel).
 bool march_few_rays(const pdrt_beam* beam, const pdrt_kernel_spec* spec, const Problem& P, size_t elem) {
   const int h = (spec->n_taps - 1) / 2;
   const long bu = std::max(1, P.Nu - 2 * h), bv = std::max(1, P.Nv - 2 * h);
@@ -288,7 +289,8 @@ void make_geo(const pdrt_grid* grid, const pdrt_beam* beam, const pdrt_kernel_sp
   g->hs_amp = (T)spec->hs_amp;
   g->oar0 = (T)spec->oar[0];
   g->oar1 = (T)spec->oar[1];
-  g->march_scan = spec->march_scan || march_few_rays(beam, spec, P, sizeof(T));
+  g->march_scan = spec->march_scan == PDRT_MARCH_SCAN ||
+                  (spec->march_scan == PDRT_MARCH_AUTO && march_few_rays(beam, spec, P, sizeof(T)));
 }
 
 // Rectangle sizes the convolutions are shaped for: with collimator angles the field

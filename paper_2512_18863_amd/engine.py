@@ -24,6 +24,9 @@ CONV_FP32 = 0
 CONV_BF16 = 1
 WEPL_PER_RAY = 0
 WEPL_CENTRAL_AXIS = 1
+MARCH_SERIAL = 0
+MARCH_SCAN = 1
+MARCH_AUTO = 2
 CACHE_F32 = 0
 CACHE_BF16 = 1
 
@@ -162,11 +165,14 @@ class DoseEngine:
 
     The CT is converted to density on the GPU once; the workspace is allocated
     once (sized for forward + backward) and reused by every call.
+
+    ``march_scan``: the form of the ray march, True the segmented scan, False one
+    thread per ray, None (default) the faster for the problem.
     """
 
     def __init__(self, case: "_inputs.Case", *, n_taps: Optional[int] = None, conv: str = "fp32",
                  wepl_mode: Optional[int] = None, device="cuda", max_cp_batch: int = 0,
-                 calib: Optional[float] = None, with_f64: bool = False, march_scan: bool = False):
+                 calib: Optional[float] = None, with_f64: bool = False, march_scan: Optional[bool] = None):
         if not torch.cuda.is_available():
             raise RuntimeError("DoseEngine needs a GPU")
         lib()
@@ -216,7 +222,7 @@ class DoseEngine:
                 s.kpoly[a][c] = float(m.kpoly[a][c])
         s.kz_max_mm = m.kz_max
         s.max_cp_batch = max_cp_batch
-        s.march_scan = 1 if march_scan else 0
+        s.march_scan = MARCH_AUTO if march_scan is None else MARCH_SCAN if march_scan else MARCH_SERIAL
         set_fluence_corrections(s, m)
         self.spec = s
         dims = (ctypes.c_int32 * 3)()

@@ -343,7 +343,7 @@ class Net3D:
 def pair(plan_index, small=9, large=61, device="cuda"):
     """(small-kernel dose, large-kernel dose, density) of a randomised 128^3 plan."""
     case = inputs.config_c4_plan(plan_index, n_taps=large)
-    e_small = E.DoseEngine(case, n_taps=small, device=device)
+    e_small = E.DoseEngine(case, n_taps=small, device=device, march_scan=False)
     e_large = E.DoseEngine(case, n_taps=large, device=device)
     dev = e_small.device
     lv = torch.tensor(case.leaves, dtype=torch.float32, device=dev)
@@ -389,7 +389,9 @@ class LearnedDose:
         assert mode in ("auto", "always", "never")
         self.mode = mode
         self.net = net
-        self.small = E.DoseEngine(case, n_taps=small)
+        # (the network's BF16 layers magnify a change in the last bits of the small-kernel dose
+        # a hundredfold: its ray march keeps one form whatever the number of rays)
+        self.small = E.DoseEngine(case, n_taps=small, march_scan=False)
         self.large = E.DoseEngine(case, n_taps=large)
         self.threshold = threshold
         self.cutoff = cutoff

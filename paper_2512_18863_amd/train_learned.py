@@ -46,7 +46,7 @@ def _t(a):
 
 def make_pair(p):
     case = inputs.config_c4_plan(p, n_taps=61)
-    es = E.DoseEngine(case, n_taps=9)
+    es = E.DoseEngine(case, n_taps=9, march_scan=False)
     el = E.DoseEngine(case, n_taps=61)
     lv, jw, mu = _t(case.leaves), _t(case.jaws), _t(case.mu)
     ds = es.forward(lv, jw, mu).reshape(-1).clone()
