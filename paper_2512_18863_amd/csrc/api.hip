@@ -222,24 +222,25 @@ int size_problem(const pdrt_grid* grid, const pdrt_beam* beam, const pdrt_kernel
 // convolutions are faster.
 constexpr int kMfmaMinTaps = 13;
 
-// PDRT_MARCH_AUTO: the segmented scan takes the ray march of problems with few rays, whose serial form
-// is one long dependent chain per ray on an otherwise idle chip.  Wavefronts of rays
-// inside the field limits, ray march and its adjoint in ms, serial / scan: 12 (one
-// field, 183 planes) 0.27 / 0.06, 383 0.28 / 0.12, 765 0.29 / 0.21, 1531 0.37 / 0.37; with
-// more planes than the scan holds at once (318) 420 0.56 / 0.29, 840 0.60 / 0.56, 1681
-// 0.68 / 1.11.  The rule looks only at what a geometry cache is tied to, so that cached
-// and uncached calls march alike; a table too long for the scan's LDS stays serial.
+// PDRT_MARCH_AUTO: problems with few rays inside the field limits (FP64: on the planes, all
+// of which that path marches) sum in the scan's order, since the serial form is one long
+// dependent chain per ray on an otherwise idle chip.  The rule looks only at what a
+// geometry cache is tied to, so that cached and uncached calls, with fluence corrections
+// or without, have the same bits; a launch that marches more rays than the limits hold (a
+// cache's whole planes, rectangles widened by the corrections) keeps the order and leaves
+// the scan (launch_march_mode).
+// A table too long for the scan's LDS stays serial.
 // Kernels of n <= 11 keep the serial form: theirs are the doses that the learned
 // correction is trained on and reads, and its BF16 layers turn a change of their last
 // bits into one a hundred times larger (the correction's own engines ask for the serial
 // form whatever the kernel).
 bool march_few_rays(const pdrt_beam* beam, const pdrt_kernel_spec* spec, const Problem& P, size_t elem) {
-  const int h = (spec->n_taps - 1) / 2;
+  const int h = elem == 8 ? 0 : (spec->n_taps - 1) / 2;
   const long bu = std::max(1, P.Nu - 2 * h), bv = std::max(1, P.Nv - 2 * h);
   const long waves = (bu * bv + 63) / 64 * beam->n_cp;
   const size_t lds = elem * (2 * kMarchMaxSegments * 64 + (size_t)spec->n_dd);
   return spec->n_taps >= kMfmaMinTaps && lds <= 64 * 1024 &&
-         waves <= (P.Nk <= kMarchSeg * kMarchMaxSegments ? 1280 : 768);
+         march_scan_wins(waves, P.Nk);
 }
 
 template <typename T>
@@ -289,8 +290,9 @@ void make_geo(const pdrt_grid* grid, const pdrt_beam* beam, const pdrt_kernel_sp
   g->hs_amp = (T)spec->hs_amp;
   g->oar0 = (T)spec->oar[0];
   g->oar1 = (T)spec->oar[1];
-  g->march_scan = spec->march_scan == PDRT_MARCH_SCAN ||
-                  (spec->march_scan == PDRT_MARCH_AUTO && march_few_rays(beam, spec, P, sizeof(T)));
+  g->march_scan = spec->march_scan == PDRT_MARCH_SCAN                                                     ? MARCH_SCAN
+                  : spec->march_scan == PDRT_MARCH_AUTO && march_few_rays(beam, spec, P, sizeof(T)) ? MARCH_SEGMENTS
+                                                                                                    : MARCH_SERIAL;
 }
 
 // Rectangle sizes the convolutions are shaped for: with collimator angles the field

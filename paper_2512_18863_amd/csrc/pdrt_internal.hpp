@@ -47,8 +47,7 @@ struct Geo {
   T hs_amp, oar0, oar1;
   int box_du, box_dv;  // pixels by which the corrections widen the aperture rectangle along u and v
   int conv_du, conv_dv;  // bound of its widening past the field limits by corrections and rotation, each side
-  // ray march: 0 = one thread per ray (serial), 1 = segmented scan across wavefronts
-  int march_scan;
+  int march_scan;  // MARCH_*: order of the ray march's sums and who computes them
 };
 
 // Unit-sum taps of one Gaussian blur, radius R <= PDRT_MAX_BLUR_RADIUS.
@@ -71,9 +70,21 @@ struct Layout {
 // cached geometry adjoint follows the same order so that both give the same bits.
 constexpr int kMarchSeg = 32;  // planes per segment and sampling pass
 constexpr int kMarchMaxSegments = 8;
+// MARCH_SEGMENTS: the scan's order, computed by the scan for launches of few rays and by
+// one thread per ray for others (the same bits).
+enum { MARCH_SERIAL = 0, MARCH_SCAN = 1, MARCH_SEGMENTS = 2 };
 __host__ __device__ inline int march_segments(int Nk) {
   const int n = (Nk + kMarchSeg - 1) / kMarchSeg;
   return n < 1 ? 1 : (n > kMarchMaxSegments ? kMarchMaxSegments : n);
+}
+
+// Wavefronts of rays up to which the scan is the faster form (launches whose rays all lie
+// in the aperture rectangles): ray march and its adjoint in ms, serial / scan, 12 (one
+// field, 183 planes) 0.27 / 0.06, 383 0.28 / 0.12, 765 0.29 / 0.21, 1531 0.37 / 0.37; with
+// more planes than the scan holds at once (318) 420 0.56 / 0.29, 840 0.60 / 0.56, 1681
+// 0.68 / 1.11.
+inline bool march_scan_wins(long waves, int Nk) {
+  return waves <= (Nk <= kMarchSeg * kMarchMaxSegments ? 1280 : 768);
 }
 
 // Raises a kernel's dynamic-LDS limit to at least `bytes` on the current device.
