@@ -31,9 +31,14 @@
 // Each wavefront owns one 16-column strip of the output and keeps its rows (the
 // box rows and two blocks above and below, for h <= 31) in registers over all tap
 // rows, then stores them; the rest of the plane (outside the strips) is written
-// with zeros.  A box larger than one chunk adds its chunks' strips into a cleared
-// plane with atomic adds, each address by its own wavefront only, in chunk order
-// (deterministic).
+// with zeros.  A box of more rows than one chunk holds is walked chunk by chunk down
+// the strip (CARRY): the chunk's rows are stored, and the four blocks that the next one
+// adds to stay in the registers.  Column chunks are loaded only where the strip is in
+// their reach.  (Where jaws inside the field limits give one row chunk, registers are
+// not kept for more: a box beyond the limits adds its chunks' strips into a cleared plane
+// with atomic adds, each address by its own wavefront only, in chunk order.)  20 control
+// points of 75 planes, 121 x 121 boxes, n = 13: 0.15 ms (0.88 with every chunk loaded for
+// every strip and atomic adds).
 //
 // One small workgroup per (control point, plane) item: its wavefronts take the strips
 // in turn, and the many workgroups of a compute unit overlap each other's taps, loads
@@ -183,8 +188,9 @@ __host__ __device__ constexpr int reg_waves(int np, int T) {
 }
 
 // T: row blocks of 16 box rows per chunk; SU: column groups per chunk (boxes larger
-// than a chunk are taken chunk by chunk).  LDS: the tap rows.
-template <int NP, int T, int SU>
+// than a chunk are taken chunk by chunk); CARRY: several row chunks expected.  LDS: the
+// tap rows.
+template <int NP, int T, int SU, bool CARRY>
 __global__ void __launch_bounds__(512, reg_waves(NP, T)) k_conv_fwd_reg(Geo<float> g, const int4* __restrict__ box,
                                                                         const float* __restrict__ zca,
                                                                         const float* __restrict__ in,
@@ -215,50 +221,47 @@ __global__ void __launch_bounds__(512, reg_waves(NP, T)) k_conv_fwd_reg(Geo<floa
   const int njt = (cw1 - cw0 + 15) / 16;
   const int nrc = (r1 - r0 + 16 * T - 1) / (16 * T), ncc = (c1 - c0 + GW * SU - 1) / (GW * SU);
 
-  // B fragments of box chunk (rc, cc): lane (n, kk) holds in[R + 16 t + n][C + 32 u
-  // + 8 kk .. + 7] as pairs of each piece.  Each run of four columns is one
-  // four-word load from a row inside the box (rows past it and runs past its last
-  // column read the box's first row or column and are cleared); a run that starts
-  // inside the box may read up to three words past its last column, i.e. past the
-  // end of the row into the next one (or, after the batch's last row, into the
-  // workspace that follows the convolution's input).
+  // B fragments of a box chunk whose first row and column are R and C: lane (n, kk) holds
+  // in[R + 16 t + n][C + 32 u + 8 kk .. + 7] as pairs of each piece.  Each run of four
+  // columns is one four-word load from a row inside the box (rows past it and runs past
+  // its last column read the box's first row or column and are cleared); a run that
+  // starts inside the box may read up to three words past its last column, i.e. past the
+  // end of the row into the next one (or, after the batch's last row, into the workspace
+  // that follows the convolution's input).
   typename Ops::BOp B;
-  auto load_b = [&](int rc, int cc) {
-    const int R = r0 + 16 * T * rc, C = c0 + GW * SU * cc;
-    auto run4 = [&](int r, int c) {
-      const f32x4u x = *reinterpret_cast<const f32x4u*>(src + (size_t)(r < r1 ? r : r0) * Nv + (c < c1 ? c : c0));
-      f32x4r v;
+  auto run4 = [&](int r, int c) {
+    const f32x4u x = *reinterpret_cast<const f32x4u*>(src + (size_t)(r < r1 ? r : r0) * Nv + (c < c1 ? c : c0));
+    f32x4r v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = (r < r1 && c + e < c1) ? x[e] : 0.f;
-      return v;
-    };
+    for (int e = 0; e < 4; ++e) v[e] = (r < r1 && c + e < c1) ? x[e] : 0.f;
+    return v;
+  };
+  auto load_b = [&](int R, int C, int t, int u) {
+    const int r = R + 16 * t + n, c = C + GW * u + 8 * kk;
+    const f32x4r x[2] = {run4(r, c), run4(r, c + 4)};
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int r = R + 16 * t + n;
+    for (int w = 0; w < 4; ++w) {
+      unsigned v[NP];
+      reg_pieces2<NP>(x[w / 2][2 * (w & 1)], x[w / 2][2 * (w & 1) + 1], v);
 #pragma unroll
-      for (int u = 0; u < SU; ++u) {
-        const int c = C + 32 * u + 8 * kk;
-        const f32x4r x[2] = {run4(r, c), run4(r, c + 4)};
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          unsigned v[NP];
-          reg_pieces2<NP>(x[w / 2][2 * (w & 1)], x[w / 2][2 * (w & 1) + 1], v);
-#pragma unroll
-          for (int i = 0; i < NP; ++i) B[i][t][u][w] = v[i];
-        }
-      }
+      for (int i = 0; i < NP; ++i) B[i][t][u][w] = v[i];
     }
   };
-  if (wave < njt) load_b(0, 0);  // in flight while the taps are built
+  const bool single = nrc == 1 && ncc == 1;
+  if (single && wave < njt) {  // in flight while the taps are built
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int u = 0; u < SU; ++u) load_b(r0, c0, t, u);
+  }
 
   clear_tap_rows(lds, h, NP, tid, NT);
   lds_barrier();
   build_tap_rows<NP>(g, k, zca[bk], lds, tid, NT, 1.f);
-  // With one chunk the strips are stored once and the plane outside them [wr0, wr1)
-  // x [cw0, cw0 + 16 njt) is zero; with several the whole plane is cleared first
-  // and the strips are added (the barrier below orders the clearing before them).
-  const bool single = nrc == 1 && ncc == 1, once = nrc == 1;
-  const int wr0 = once ? r0 - 16 * kRegQB : 0, wr1 = once ? r0 + 16 * (T + kRegQB) : 0;
+  // zeros outside the strips' window [wr0, wr1) x [cw0, cw0 + 16 njt); where strips are
+  // added, in the whole plane (the barrier below orders them)
+  const bool store = CARRY || nrc == 1;
+  const int wr0 = store ? r0 - 16 * kRegQB : 0, wr1 = store ? r0 + 16 * (T * nrc + kRegQB) : 0;
   {
     // whole rows above and below the window (two contiguous ranges), then the
     // columns left and right of it in the rows between
@@ -272,18 +275,21 @@ __global__ void __launch_bounds__(512, reg_waves(NP, T)) k_conv_fwd_reg(Geo<floa
       dst[(size_t)(zr0 + rr) * Nv + (cc < cw0 ? cc : cz1 + (cc - cw0))] = 0.f;
     }
   }
-  if (once) lds_barrier();
+  if (store) lds_barrier();
   else __syncthreads();
 
   for (int jt = wave; jt < njt; jt += nw) {
     const int J = cw0 + 16 * jt;  // the strip's first output column
+    f32x4r O[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) O[q] = f32x4r{0.f, 0.f, 0.f, 0.f};
     for (int rc = 0; rc < nrc; ++rc) {
       const int R = r0 + 16 * T * rc;
-      f32x4r O[NB];
+      if constexpr (!CARRY) {
 #pragma unroll
-      for (int q = 0; q < NB; ++q) O[q] = f32x4r{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < NB; ++q) O[q] = f32x4r{0.f, 0.f, 0.f, 0.f};
+      }
       for (int cc = 0; cc < ncc; ++cc) {
-        if (!single && (jt != wave || rc != 0 || cc != 0)) load_b(rc, cc);
         const int C = c0 + GW * SU * cc;
         const int nsu = min(SU, (c1 - C + GW - 1) / GW);
         // column groups with a column within h of the strip [J, J + 16)
@@ -291,6 +297,20 @@ __global__ void __launch_bounds__(512, reg_waves(NP, T)) k_conv_fwd_reg(Geo<floa
         const int ua = lo <= 0 ? 0 : (lo + GW - 1) / GW;
         const int ub = min(nsu - 1, hi >= 0 ? hi / GW : -1);
         if (ua > ub) continue;
+        if (!single) {  // the groups in reach; zeros in the others (group 0 is multiplied always)
+#pragma unroll
+          for (int u = 0; u < SU; ++u) {
+            if (u >= ua && u <= ub) {
+#pragma unroll
+              for (int t = 0; t < T; ++t) load_b(R, C, t, u);
+            } else {
+#pragma unroll
+              for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int i = 0; i < NP; ++i) B[i][t][u] = u32x4r{0u, 0u, 0u, 0u};
+            }
+          }
+        }
         // A of group u in tap row p starts at x = C + 32 u + 8 kk - J - m + kRegOff (m
         // the lane's output column), moved to a run of zeros where it meets no tap
         // (so group 0 runs also out of reach; the others are skipped)
@@ -309,26 +329,31 @@ __global__ void __launch_bounds__(512, reg_waves(NP, T)) k_conv_fwd_reg(Geo<floa
         reg_tap_rows<NP, 0, T, SU, NB>(h, aaddr, umask, A, B, O);
       }
       // the strip's rows R - 16 kRegQB + 16 q + n and columns J + 4 kk + e that lie in
-      // the plane (stored with one row chunk, added with several); only this wavefront
-      // writes them
+      // the plane; only this wavefront writes them (CARRY: the four lower blocks stay for the
+      // next chunk, which stores them again: a test for the last chunk costs the registers
+      // of a second copy)
 #pragma unroll
       for (int q = 0; q < NB; ++q) {
         const int row = R - 16 * kRegQB + 16 * q + n;
         if (row >= 0 && row < Nu) {
           float* o = dst + (size_t)row * Nv + J + 4 * kk;
-          if (once && J + 4 * kk + 3 < Nv) {
+          if (store && J + 4 * kk + 3 < Nv) {
             *reinterpret_cast<f32x4u*>(o) = O[q];  // the lane's four consecutive columns
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float v = O[q][e];
               if (J + 4 * kk + e < Nv) {
-                if (once) o[e] = v;
+                if (store) o[e] = v;
                 else unsafeAtomicAdd(o + e, v);
               }
             }
           }
         }
+      }
+      if constexpr (CARRY) {
+#pragma unroll
+        for (int q = 0; q < NB; ++q) O[q] = q + T < NB ? O[q + T] : f32x4r{0.f, 0.f, 0.f, 0.f};
       }
     }
   }
@@ -340,11 +365,11 @@ bool conv_fwd_reg_supported(const Geo<float>& g, bool bf16) {
   return g.h >= 1 && g.h <= kRegMaxH && reg_lds(g.h, bf16) <= 160 * 1024;
 }
 
-template <int NP, int T, int SU>
+template <int NP, int T, int SU, bool CARRY = false>
 static hipError_t launch_reg_cfg(const Geo<float>& g, int nb, const int4* box, const float* z, const float* in,
                                  float* out, hipStream_t s) {
   const size_t lds = reg_lds(g.h, NP == 1);
-  const void* kern = (const void*)k_conv_fwd_reg<NP, T, SU>;
+  const void* kern = (const void*)k_conv_fwd_reg<NP, T, SU, CARRY>;
   {
     hipError_t e = ensure_lds_limit(kern, (int)lds);
     if (e != hipSuccess) return e;
@@ -355,13 +380,20 @@ static hipError_t launch_reg_cfg(const Geo<float>& g, int nb, const int4* box, c
   // ms); else two for the short loops of small kernels (90 control points, n = 15: 0.095
   // against 0.117 ms), four for larger ones (180, n = 61: 1.07 against 1.26 ms)
   const int nw = n_items <= 2 * device_cus() ? 8 : g.h <= 16 ? 2 : 4;
-  hipLaunchKernelGGL((k_conv_fwd_reg<NP, T, SU>), dim3((unsigned)n_items), dim3(64 * nw), lds, s, g, box, z, in, out);
+  hipLaunchKernelGGL((k_conv_fwd_reg<NP, T, SU, CARRY>), dim3((unsigned)n_items), dim3(64 * nw), lds, s, g, box, z, in, out);
   return hipGetLastError();
 }
 
 template <int NP>
 static hipError_t launch_reg_np(const Geo<float>& g, int nb, const int4* box, const float* z, const float* in,
-                                float* out, hipStream_t s, int ch) {
+                                float* out, hipStream_t s, int ch, int chunks) {
+  if (chunks > 1) {
+    switch (ch) {
+      case 4: return launch_reg_cfg<NP, 4, 2, true>(g, nb, box, z, in, out, s);
+      case 5: return launch_reg_cfg<NP, 5, 2, true>(g, nb, box, z, in, out, s);
+      default: return launch_reg_cfg<NP, 6, 2, true>(g, nb, box, z, in, out, s);
+    }
+  }
   switch (ch) {
     case 1: return launch_reg_cfg<NP, 1, 1>(g, nb, box, z, in, out, s);
     case 2: return launch_reg_cfg<NP, 2, 1>(g, nb, box, z, in, out, s);
@@ -375,8 +407,9 @@ static hipError_t launch_reg_np(const Geo<float>& g, int nb, const int4* box, co
 // The chunk shape from the largest rectangle that jaws inside the field limits give,
 // widened by fluence corrections and collimator rotation: one row chunk of up to six
 // blocks, else equal chunks; columns beyond two groups come in column chunks, summed in
-// registers.  (n = 61, 180 control points, 71 x 71 boxes: 5.4 ms with five blocks, 9.5 in
-// two chunks of four, 10.1 of three; all columns at once leave one wavefront per SIMD.)
+// registers.  (n = 61, 40 control points of 75 planes, 81 x 81 boxes: 0.68 ms with six
+// blocks, 0.72 in two chunks of three, 0.94 of four; all columns at once leave one
+// wavefront per SIMD.)
 hipError_t launch_conv_fwd_reg(const Geo<float>& g, int nb, const float* z, const float* in, float* out,
                                hipStream_t s, const int* box, bool bf16) {
   if (!conv_fwd_reg_supported(g, bf16) || !box) return hipErrorInvalidConfiguration;
@@ -386,7 +419,8 @@ hipError_t launch_conv_fwd_reg(const Geo<float>& g, int nb, const float* z, cons
   const int bc = min(g.Nv, 2 * (half_v > 0 ? half_v : 0) + 1 + 2 * g.conv_dv);
   const int blocks = ((br > bc ? br : bc) + 15) / 16, chunks = (blocks + 5) / 6;
   const int ch = (blocks + chunks - 1) / chunks;
-  return bf16 ? launch_reg_np<1>(g, nb, bx, z, in, out, s, ch) : launch_reg_np<3>(g, nb, bx, z, in, out, s, ch);
+  return bf16 ? launch_reg_np<1>(g, nb, bx, z, in, out, s, ch, chunks)
+              : launch_reg_np<3>(g, nb, bx, z, in, out, s, ch, chunks);
 }
 
 }  // namespace pdrt

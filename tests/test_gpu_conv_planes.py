@@ -1,0 +1,184 @@
+"""The matrix-core convolutions plane by plane, on every pixel that they write: the output
+left in the workspace against an FP64 convolution of the input left there, with the
+oracle's taps at the workspace's depths.
+
+Forms: one to six row blocks in one chunk, seven and more in several (carried down the
+strip), columns in several chunks, jaws beyond the field limit (more chunks than the
+launch expects), rectangles of one tile to several pieces of four by four, turned and
+widened rectangles, few and many items.  Bars, of the largest output: FP32 5e-6 (that of
+the intermediates' test), BF16 2^-8 (operands rounded to 8 bits).
+
+Accuracy: FP32 operands travel as three BF16 pieces in six products.  With a kernel whose
+centre tap holds 95 % of the sum an output is one product, and a lost or misplaced third
+piece shows at its full size, up to 2^-17 of it (a model below drops each product in
+turn: 3e-6 to 2e-5).  The bar is 1.5e-6: the centre tap's evaluation in FP32 (four
+roundings of 2^-24 and two exponentials of 2^-22) and the sum's rounding take up to 8e-7."""
+import copy
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2512_18863_amd import inputs
+
+
+def _case(n_taps, ju, jv, limit, n_cp=2, corr=False, coll=False, narrow=False):
+    """2.5 mm pixels, 25 mm between planes; the grid covers the field, so that the adjoint's
+    input does too."""
+    d, half = 2.5, max(limit, ju, jv)
+    nz, nxy = int(2 * half) + 3, min(60, int(2 * half * d / 5.0) + 3)
+    c = inputs.tiny_case(seed=n_taps + int(ju), n_cp=n_cp, n_taps=n_taps, shape=(nz, nxy, nxy + 1), spacing=d,
+                         field=limit * d, n_leaf=14, leaf_width=2.0 * max(jv, 4.0) * d / 14)
+    c = copy.copy(c)
+    c.spacing = (5.0, 5.0, d)
+    c.origin = tuple(-(n - 1) / 2.0 * s for n, s in zip(c.shape[::-1], c.spacing))
+    c.lat_step, c.depth_step = d, 25.0
+    rng = np.random.default_rng(n_taps)
+    c.jaws = inputs.jaws_square(n_cp, ju * d, jv * d) + rng.uniform(-0.3, 0.3, size=(n_cp, 1)) * d
+    c.leaves = inputs.random_apertures(n_cp, 14, max(ju * d, 1.0), seed=3, max_gap=2.0 * ju * d)
+    if corr:
+        c.machine = inputs.with_fluence_corrections(c.machine)
+    if coll:
+        c.collimator = rng.uniform(-45.0, 45.0, size=n_cp)
+    if narrow:  # exp(-2 r): the disc of the centre tap holds 95 %
+        k = np.zeros((4, 4))
+        k[:, 0] = (1.0, 2.0, 0.1, 2.5)
+        c.machine = dataclasses.replace(c.machine, kpoly=k)
+    return c
+
+
+def _error(c, conv, way):
+    """(largest |output - FP64| over the pixels written, of the largest output; planes' shape)"""
+    from paper_2512_18863_amd.engine import DoseEngine
+    from tests.test_gpu_parity import _t
+    eng = DoseEngine(c, conv=conv)
+    p, n = (_t(c.leaves), _t(c.jaws), _t(c.mu)), c.n_cp
+    if way == "forward":
+        eng.forward(*p)
+    else:
+        eng.backward(*p, _t(np.random.default_rng(5).uniform(0.5, 1.0, size=c.shape)))
+    torch.cuda.synchronize()
+    Nk, Nu, Nv = eng.fan_shape()
+    view = lambda name, shape, **kw: eng.ws_view(name, shape, with_backward=int(way != "forward"), **kw)
+    x, y = (view(v, (n, Nk, Nu, Nv)) for v in ("vol0", "vol1"))
+    z = view("depth", (n, Nk)).cpu().numpy().astype(np.float64)
+    box = view("box", (n, 4), dtype=torch.int32).cpu().numpy()
+    m, h = oracle.Model(c), (c.n_taps - 1) // 2
+    size = [s + c.n_taps - 1 for s in (Nu, Nv)]
+    worst = top = 0.0
+    for b in range(0, n, max(1, n // 2)):
+        u0, u1, v0, v1 = box[b]
+        for k in sorted({0, Nk // 3, Nk // 2, Nk - 1}):
+            K = torch.tensor(oracle.taps(m, m.d0 + k * c.depth_step, z[b, k]), device="cuda")
+            src = x[b, k].double()
+            if way == "forward":
+                src = torch.zeros_like(src)
+                src[u0:u1, v0:v1] = x[b, k, u0:u1, v0:v1].double()
+            full = torch.fft.irfft2(torch.fft.rfft2(src, s=size) * torch.fft.rfft2(K, s=size), s=size)
+            ref = full[h:h + Nu, h:h + Nv]
+            e = (y[b, k].double() - ref).abs()
+            if way != "forward":  # (outputs are needed, and written, inside the rectangle)
+                e, ref = e[u0:u1, v0:v1], ref[u0:u1, v0:v1]
+            assert bool(torch.isfinite(e).all())
+            worst, top = max(worst, float(e.max())), max(top, float(ref.abs().max()))
+    return worst / top, (Nk, Nu, Nv), [int((box[:, 1] - box[:, 0]).max()), int((box[:, 3] - box[:, 2]).max())]
+
+
+# (kernel width, jaw half-widths in pixels along u and v, field limit in pixels, control points, corrections, collimator)
+CASES = [
+    (13, 0.4, 3.3, 6, 2, 0, 0), (15, 7.4, 7.6, 8, 2, 0, 0), (31, 15.7, 16.4, 17, 2, 0, 0), (33, 20.2, 24.4, 25, 2, 0, 0),
+    (61, 24.6, 31.8, 32, 2, 0, 0), (63, 13.3, 13.3, 14, 2, 0, 0), (21, 32.6, 40.3, 41, 2, 0, 0),
+    (13, 47.2, 47.2, 48, 2, 0, 0), (15, 52.2, 50.4, 53, 2, 0, 0), (61, 62.7, 63.1, 64, 2, 0, 0),
+    (33, 74.2, 30.0, 75, 2, 0, 0), (13, 101.0, 100.3, 102, 1, 0, 0), (45, 20.0, 30.0, 110, 2, 0, 0),
+    (15, 20.0, 20.0, 5, 2, 0, 0), (13, 40.0, 44.0, 10, 2, 0, 0), (61, 30.0, 30.0, 9, 2, 0, 0),
+    (13, 9.3, 12.2, 13, 2, 1, 0), (31, 30.2, 28.1, 31, 2, 1, 0), (15, 9.3, 12.2, 13, 2, 0, 1),
+    (17, 30.3, 29.2, 31, 2, 0, 1), (13, 39.3, 38.2, 40, 2, 1, 1), (61, 20.3, 20.2, 21, 2, 1, 1),
+    (13, 3.3, 5.2, 6, 90, 0, 0), (31, 8.3, 8.2, 9, 90, 0, 0),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("way", ["forward", "adjoint"])
+@pytest.mark.parametrize("kw", CASES, ids=["%d-%g-%g-%d-%d-%d%d" % c for c in CASES])
+def test_every_pixel_of_the_planes(kw, way):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests.test_gpu_parity import _say
+    c = _case(*kw)
+    for conv, tol in (("fp32", 5e-6), ("bf16", 2.0 ** -8)):
+        e, planes, box = _error(c, conv, way)
+        _say("%s %s n %d, planes %d x %d x %d, boxes up to %d x %d: %.2e" % ((way, conv, c.n_taps) + planes +
+                                                                            (box[0], box[1], e)))
+        assert e <= tol
+
+
+NARROW = [(13, 7.4, 7.6, 8), (31, 20.2, 24.4, 25), (61, 24.6, 31.8, 32), (55, 32.6, 40.3, 41), (15, 62.7, 63.1, 64)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("way", ["forward", "adjoint"])
+@pytest.mark.parametrize("n_taps,ju,jv,limit", NARROW)
+def test_fp32_products_keep_24_bits(n_taps, ju, jv, limit, way):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests.test_gpu_parity import _say
+    e, planes, _ = _error(_case(n_taps, ju, jv, limit, narrow=True), "fp32", way)
+    _say("%s, narrow kernel, n %d, planes %d x %d x %d: %.2e" % ((way, n_taps) + planes + (e,)))
+    assert e <= 1.5e-6
+
+
+def _bf16(x):
+    """float32 values rounded to BF16 (nearest even)."""
+    u = np.ascontiguousarray(x, dtype=np.float32).view(np.uint32)
+    return ((u + 0x7fff + ((u >> 16) & 1)) & 0xffff0000).astype(np.uint32).view(np.float32)
+
+
+def _pieces(x):
+    out, rest = [], np.asarray(x, dtype=np.float32)
+    for _ in range(3):
+        out.append(_bf16(rest))
+        rest = (rest - out[-1]).astype(np.float32)
+    assert not rest.any()  # three pieces hold an FP32 number exactly
+    return [p.astype(np.float64) for p in out]
+
+
+def test_lost_products_show_in_the_narrow_kernel():
+    """Six products are within the bound stated for the three left out; each one lost exceeds
+    the accuracy bar by a factor of two at least."""
+    rng = np.random.default_rng(0)
+    x, y = (rng.uniform(1.0, 2.0, size=200000).astype(np.float32) for _ in range(2))
+    px, py, exact = _pieces(x), _pieces(y), x.astype(np.float64) * y.astype(np.float64)
+    six = [(0, 0), (0, 1), (1, 0), (1, 1), (0, 2), (2, 0)]
+    rel = lambda keep: (np.abs(sum(px[i] * py[j] for i, j in keep) - exact) / exact).max()
+    assert rel(six) <= 2.0 ** -24
+    x1, x2 = (np.abs(px[i]) / x for i in (1, 2))
+    assert x1.max() <= 2.0 ** -8 and x2.max() <= 2.0 ** -16.99
+    for lost in six[1:]:
+        assert 0.95 * rel([p for p in six if p != lost]) >= 2 * 1.5e-6, lost
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("conv", ["fp32", "bf16"])
+def test_wide_rectangles_cost_by_their_area(conv):
+    """Twice the pixels in half the control points: the forward convolution of a small kernel
+    takes about as long over several row and column chunks as over one."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2512_18863_amd import engine as E
+    from tests.test_gpu_parity import _say, _t
+    ms = {}
+    for px, n_cp in ((40, 40), (60, 20)):
+        c = inputs.tiny_case(seed=3, n_cp=n_cp, n_taps=13, shape=(16, 48, 56), spacing=2.5, field=2.5 * px, n_leaf=14,
+                             leaf_width=2.0 * px * 2.5 / 14)
+        c.jaws = inputs.jaws_square(n_cp, 2.5 * px, 2.5 * px)
+        eng = E.DoseEngine(c, conv=conv)
+        p, best = (_t(c.leaves), _t(c.jaws), _t(c.mu)), float("inf")
+        for _ in range(8):
+            E.profile_begin(64)
+            eng.forward(*p)
+            best = min(best, E.profile_end()["conv_mfma_f32" if conv == "fp32" else "conv_mfma_bf16"][1])
+        _say("%s forward, %d control points of %d x %d: %.4f ms" % (conv, n_cp, 2 * px + 1, 2 * px + 1, best))
+        ms[px] = best
+    assert ms[60] <= 2.5 * ms[40]  # (five times as long with every chunk loaded for every strip)
