@@ -14,8 +14,8 @@
 // exact, FP32 sums).  Folding the two rows first halves the matrix work; the split is
 // done in the vector unit, which the matrix instructions leave free.
 //
-// One workgroup per (control point, plane) item and piece; its wavefronts share the
-// (column group, tap row) pairs evenly, each for all T x CB tiles, so a split feeds CB
+// One workgroup per (control point, plane) item and piece; a rectangle's pieces have equal
+// numbers of tiles.  Its wavefronts share the (column group, tap row) pairs evenly, each for all T x CB tiles, so a split feeds CB
 // tiles and a tap run T.  Their sums are added in LDS in wavefront order, one row of
 // tiles at a time.  (Wavefronts come in multiples of four: a workgroup of six, two on
 // two of the SIMDs, kept a second one off the compute unit.)
@@ -53,7 +53,7 @@ __global__ void __launch_bounds__(512, T <= 2 ? 5 : T == 3 ? 4 : 2) k_conv_adj(G
                                                       const float* __restrict__ zca, const float* __restrict__ in,
                                                       float* __restrict__ out) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int h = g.h, h1 = h + 1, rows = adj_img_rows(T, h);
+  const int h = g.h, h1 = h + 1;
   const int CS = h1 * NP * kRegW;
   unsigned* taps = reinterpret_cast<unsigned*>(smem_raw);
   float* img = reinterpret_cast<float*>(taps + reg_tap_words(h, NP));
@@ -67,7 +67,12 @@ __global__ void __launch_bounds__(512, T <= 2 ? 5 : T == 3 ? 4 : 2) k_conv_adj(G
   const int4 bx = box[b];
   const int r0 = max(bx.x, 0), r1 = min(bx.y, Nu), c0 = max(bx.z, 0), c1 = min(bx.w, Nv);
   if (r1 <= r0 || c1 <= c0) return;
-  const int npi = (r1 - r0 + 16 * T - 1) / (16 * T), npj = (c1 - c0 + 16 * CB - 1) / (16 * CB);
+  // pieces of equal numbers of tiles, tr x tc
+  const int nr = (r1 - r0 + 15) / 16, nc = (c1 - c0 + 15) / 16;
+  const int npi = (nr + T - 1) / T, npj = (nc + CB - 1) / CB;
+  int tr = nr, tc = nc;
+  if (npi > 1) tr = (nr + npi - 1) / npi;
+  if (npj > 1) tc = (nc + npj - 1) / npj;
   if ((int)blockIdx.y >= npi * npj) return;
   const float* src = in + (size_t)bk * plane;
   float* dst = out + (size_t)bk * plane;
@@ -76,20 +81,22 @@ __global__ void __launch_bounds__(512, T <= 2 ? 5 : T == 3 ? 4 : 2) k_conv_adj(G
   bool built = false;
 
   for (int pp = blockIdx.y; pp < npi * npj; pp += gridDim.y) {
-    const int I = r0 + 16 * T * (pp / npj), J = c0 + 16 * CB * (pp % npj);
-    // the window: plane rows I - h + [0, rows), columns wc0 + [0, 32 ng), zero outside the
-    // plane; a four-column group that starts inside a row may read up to three words past
-    // its end (the next row, or after the batch's last row the workspace that follows)
-    const int wc0 = max(0, J - h), wc1 = min(Nv, min(J + 16 * CB, c1) + h);
+    const int I = r0 + 16 * tr * (pp / npj), J = c0 + 16 * tc * (pp % npj);
+    const int I1 = min(I + 16 * tr, r1), J1 = min(J + 16 * tc, c1);
+    // the window: plane rows I - h + [0, 16 tr + 2 h), zero outside the plane, and columns
+    // [wc0, wc1), zero up to the end of their last group; a four-column group that starts
+    // inside a row may read up to three words past its end (the next row, or after the
+    // batch's last row the workspace that follows)
+    const int wc0 = max(0, J - h), wc1 = min(Nv, J1 + h);
     const int ng = (wc1 - wc0 + 31) / 32, gw = 8 * ng;
-    for (RectWalk w(tid, NT, gw); w.r < rows; w.next(gw)) {
+    for (RectWalk w(tid, NT, gw); w.r < 16 * tr + 2 * h; w.next(gw)) {
       const int r = w.r, q = w.c;
       const int pr = I - h + r, pc = wc0 + 4 * q;
       f32x4a v = {0.f, 0.f, 0.f, 0.f};
-      if (pr >= 0 && pr < Nu && pc < Nv) {
+      if (pr >= 0 && pr < Nu && pc < wc1) {
         const f32x4ua x = *reinterpret_cast<const f32x4ua*>(src + (size_t)pr * Nv + pc);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = pc + c < Nv ? x[c] : 0.f;
+        for (int c = 0; c < 4; ++c) v[c] = pc + c < wc1 ? x[c] : 0.f;
       }
       *reinterpret_cast<f32x4a*>(img + r * pitch + 4 * q) = v;
     }
@@ -188,7 +195,7 @@ __global__ void __launch_bounds__(512, T <= 2 ? 5 : T == 3 ? 4 : 2) k_conv_adj(G
     typedef std::integral_constant<int, (T > 1 ? T - 1 : 1)> ST;
     typedef std::integral_constant<int, CB> FC;
     typedef std::integral_constant<int, (CB > 1 ? CB - 1 : 1)> SC;
-    const bool st = r1 - I <= 16 * (T - 1), sc = c1 - J <= 16 * (CB - 1);
+    const bool st = I1 - I <= 16 * (T - 1), sc = J1 - J <= 16 * (CB - 1);
     if (st) {
       if (sc) products(ST(), SC());
       else products(ST(), FC());
@@ -208,10 +215,10 @@ __global__ void __launch_bounds__(512, T <= 2 ? 5 : T == 3 ? 4 : 2) k_conv_adj(G
         f32x4a v = sums[c * 64 + lane];
         for (int w = 1; w < nw; ++w) v += sums[(w * CB + c) * 64 + lane];
         const int i = I + 16 * t + n, j = J + 16 * c + 4 * kk;
-        if (i < Nu) {
+        if (i < min(I + 16 * tr, Nu)) {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            if (j + e < Nv) dst[(size_t)i * Nv + j + e] = v[e];
+            if (j + e < min(J + 16 * tc, Nv)) dst[(size_t)i * Nv + j + e] = v[e];
         }
       }
     }
@@ -219,13 +226,55 @@ __global__ void __launch_bounds__(512, T <= 2 ? 5 : T == 3 ? 4 : 2) k_conv_adj(G
   }
 }
 
+// Wavefronts of a workgroup and its LDS for pieces of n x n tiles.
+int adj_waves(int np, int n, int h) { return h <= 16 || (n == 4 && (np == 1 || h <= 24)) ? 4 : 8; }
+int adj_pitch(const Geo<float>& g, int n) { return (min(g.Nv, 16 * n + 2 * g.h) + 31) / 32 * 32 + 8; }
+size_t adj_lds(const Geo<float>& g, int np, int n) {
+  const size_t img = sizeof(float) * (size_t)adj_img_rows(n, g.h) * adj_pitch(g, n);
+  const size_t red = (size_t)adj_waves(np, n, g.h) * n * 1024;
+  return sizeof(unsigned) * (size_t)reg_tap_words(g.h, np) + (img > red ? img : red);
+}
+
+// Tiles per side of a piece for rectangles of side `side` pixels: one piece up to three
+// tiles; above, the least of column groups over all pieces x time of a (group, tap row)
+// pair, measured relative to pieces of two: three 1.6 and four 3.0 (BF16: 1.5, 2.2),
+// pieces that are a tile smaller than their kernel 0.8 (0.7) of that, and 1.5 where FP32
+// windows of two or three leave one workgroup to a compute unit.  FP32, 75 planes each:
+//   60 control points, n = 13, 57 x 57 pixels  0.136 ms in pieces of 2, 0.164 of 3, 0.156 of 4
+//   20, n = 13, 121 x 121                      0.168, 0.148, 0.191
+//   60, n = 45, 57 x 57                        0.53, 0.58, 0.46
+//   60, n = 61, 57 x 57                        0.66, 1.03, 0.76
+//   40, n = 55, 103 x 103 (corrections)        1.24, 1.74, 1.17
+int adj_tiles(const Geo<float>& g, int np, double side) {
+  const int blocks = (int)ceil(side / 16.0);
+  if (blocks <= 3) return blocks > 1 ? blocks : 1;
+  const double pair[5] = {0.0, 0.0, 1.0, np == 3 ? 1.6 : 1.5, np == 3 ? 3.0 : 2.2};
+  const double c0 = 0.5 * (g.Nv - side);  // the rectangle's first column
+  int best = 2;
+  double least = 1e30;
+  for (int n = 2; n <= 4; ++n) {
+    const int m = (blocks + n - 1) / n, tiles = (blocks + m - 1) / m;
+    double groups = 0.0;
+    for (int j = 0; j < m; ++j) {
+      const double a = fmax(0.0, c0 + 16 * tiles * j - g.h);
+      const double b = fmin(g.Nv, fmin(c0 + 16 * tiles * (j + 1), c0 + side) + g.h);
+      groups += fmax(1.0, ceil((b - a) / 32.0 - 1e-9));
+    }
+    double cost = m * groups * pair[n];
+    if (tiles < n) cost *= np == 3 ? 0.8 : 0.7;
+    if (np == 3 && n < 4 && adj_lds(g, np, n) > 80 * 1024) cost *= 1.5;
+    if (cost < least) {
+      least = cost;
+      best = n;
+    }
+  }
+  return best;
+}
+
 template <int NP, int N>
 hipError_t launch_adj_cfg(const Geo<float>& g, int nb, int pieces, const int4* box, const float* z, const float* in,
                           float* out, hipStream_t s) {
-  const int pitch = (min(g.Nv, 16 * N + 2 * g.h) + 31) / 32 * 32 + 8;
-  const int nw = g.h <= 16 ? 4 : 8;
-  const size_t img = sizeof(float) * (size_t)adj_img_rows(N, g.h) * pitch, red = (size_t)nw * N * 1024;
-  const size_t lds = sizeof(unsigned) * (size_t)reg_tap_words(g.h, NP) + (img > red ? img : red);
+  const size_t lds = adj_lds(g, NP, N);
   if (lds > 160 * 1024) return hipErrorInvalidConfiguration;
   const void* kern = (const void*)k_conv_adj<NP, N, N>;
   {
@@ -234,41 +283,42 @@ hipError_t launch_adj_cfg(const Geo<float>& g, int nb, int pieces, const int4* b
   }
   const long n_items = (long)nb * g.Nk;
   if (n_items > 0x7fffffffL) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k_conv_adj<NP, N, N>), dim3((unsigned)n_items, pieces), dim3(64 * nw), lds, s, g, pitch, box, z, in,
-                     out);
+  hipLaunchKernelGGL((k_conv_adj<NP, N, N>), dim3((unsigned)n_items, pieces), dim3(64 * adj_waves(NP, N, g.h)), lds, s, g,
+                     adj_pitch(g, N), box, z, in, out);
   return hipGetLastError();
+}
+
+template <int NP>
+hipError_t launch_adj_np(const Geo<float>& g, int nb, const int4* box, const float* z, const float* in, float* out,
+                         hipStream_t s) {
+  // the largest rectangle that jaws inside the field limits give, widened by fluence
+  // corrections and collimator rotation, sets the number of workgroups per item (a larger
+  // one has them take several pieces); the usual one, of openings a little inside the
+  // limits and angles short of the diagonal, the pieces' size
+  const int half_u = (g.Nu - 1) / 2 - g.h, half_v = (g.Nv - 1) / 2 - g.h;  // field limit in pixels
+  const int fu = 2 * (half_u > 0 ? half_u : 0) + 1, fv = 2 * (half_v > 0 ? half_v : 0) + 1;
+  const int br = min(g.Nu, fu + 2 * g.conv_du), bc = min(g.Nv, fv + 2 * g.conv_dv);
+  const double turned = g.conv_du == g.box_du && g.conv_dv == g.box_dv ? 1.0 : 0.7;
+  const double ur = fmin(g.Nu, 0.95 * fu + 2 * turned * g.conv_du), uc = fmin(g.Nv, 0.95 * fv + 2 * turned * g.conv_dv);
+  const int n = adj_tiles(g, NP, fmax(ur, uc));
+  const int pieces = ((br + 16 * n - 1) / (16 * n)) * ((bc + 16 * n - 1) / (16 * n));
+  switch (n) {
+    case 1: return launch_adj_cfg<NP, 1>(g, nb, pieces, box, z, in, out, s);
+    case 2: return launch_adj_cfg<NP, 2>(g, nb, pieces, box, z, in, out, s);
+    case 3: return launch_adj_cfg<NP, 3>(g, nb, pieces, box, z, in, out, s);
+    default: return launch_adj_cfg<NP, 4>(g, nb, pieces, box, z, in, out, s);
+  }
 }
 
 }  // namespace
 
 bool conv_adj_supported(const Geo<float>& g) { return g.h >= 1 && g.h <= kRegMaxH; }
 
-// Pieces of N x N tiles for the largest rectangle that jaws inside the field limits
-// give, widened by fluence corrections and collimator rotation (N <= 4; equal pieces); a rectangle
-// larger than that has its workgroups take several pieces.
 hipError_t launch_conv_adj(const Geo<float>& g, int nb, const float* z, const float* in, float* out, hipStream_t s,
                            const int* box, bool bf16) {
   if (!conv_adj_supported(g) || !box) return hipErrorInvalidConfiguration;
   const int4* bx = reinterpret_cast<const int4*>(box);
-  const int half_u = (g.Nu - 1) / 2 - g.h, half_v = (g.Nv - 1) / 2 - g.h;  // field limit in pixels
-  const int br = min(g.Nu, 2 * (half_u > 0 ? half_u : 0) + 1 + 2 * g.conv_du);
-  const int bc = min(g.Nv, 2 * (half_v > 0 ? half_v : 0) + 1 + 2 * g.conv_dv);
-  const int blocks = ((br > bc ? br : bc) + 15) / 16, per = (blocks + 3) / 4, n = (blocks + per - 1) / per;
-  const int pieces = ((br + 16 * n - 1) / (16 * n)) * ((bc + 16 * n - 1) / (16 * n));
-  if (bf16) {
-    switch (n) {
-      case 1: return launch_adj_cfg<1, 1>(g, nb, pieces, bx, z, in, out, s);
-      case 2: return launch_adj_cfg<1, 2>(g, nb, pieces, bx, z, in, out, s);
-      case 3: return launch_adj_cfg<1, 3>(g, nb, pieces, bx, z, in, out, s);
-      default: return launch_adj_cfg<1, 4>(g, nb, pieces, bx, z, in, out, s);
-    }
-  }
-  switch (n) {
-    case 1: return launch_adj_cfg<3, 1>(g, nb, pieces, bx, z, in, out, s);
-    case 2: return launch_adj_cfg<3, 2>(g, nb, pieces, bx, z, in, out, s);
-    case 3: return launch_adj_cfg<3, 3>(g, nb, pieces, bx, z, in, out, s);
-    default: return launch_adj_cfg<3, 4>(g, nb, pieces, bx, z, in, out, s);
-  }
+  return bf16 ? launch_adj_np<1>(g, nb, bx, z, in, out, s) : launch_adj_np<3>(g, nb, bx, z, in, out, s);
 }
 
 }  // namespace pdrt

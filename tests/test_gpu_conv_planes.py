@@ -95,6 +95,7 @@ CASES = [
     (15, 20.0, 20.0, 5, 2, 0, 0), (13, 40.0, 44.0, 10, 2, 0, 0), (61, 30.0, 30.0, 9, 2, 0, 0),
     (13, 9.3, 12.2, 13, 2, 1, 0), (31, 30.2, 28.1, 31, 2, 1, 0), (15, 9.3, 12.2, 13, 2, 0, 1),
     (17, 30.3, 29.2, 31, 2, 0, 1), (13, 39.3, 38.2, 40, 2, 1, 1), (61, 20.3, 20.2, 21, 2, 1, 1),
+    (45, 27.2, 27.4, 28, 2, 0, 0), (13, 30.4, 31.2, 32, 2, 0, 0), (55, 29.3, 33.4, 34, 2, 0, 0),
     (13, 3.3, 5.2, 6, 90, 0, 0), (31, 8.3, 8.2, 9, 90, 0, 0),
 ]
 
@@ -182,3 +183,29 @@ def test_wide_rectangles_cost_by_their_area(conv):
         _say("%s forward, %d control points of %d x %d: %.4f ms" % (conv, n_cp, 2 * px + 1, 2 * px + 1, best))
         ms[px] = best
     assert ms[60] <= 2.5 * ms[40]  # (five times as long with every chunk loaded for every strip)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("conv,most", [("fp32", 2.5), ("bf16", 1.9)])
+def test_wide_adjoint_pieces(conv, most):
+    """The adjoint of 65 x 65 pixels in two thirds of the control points against 41 x 41
+    (1.6 times the pixels in all): about 1.6 and 1.4 times as long with pieces of the better
+    size, 3.6 and 2.5 times with the largest ones."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2512_18863_amd import engine as E
+    from tests.test_gpu_parity import _say, _t
+    ms = {}
+    for px, n_cp in ((20, 60), (32, 40)):
+        c = inputs.tiny_case(seed=3, n_cp=n_cp, n_taps=55, shape=(16, 48, 56), spacing=2.5, field=2.5 * px, n_leaf=14,
+                             leaf_width=2.0 * px * 2.5 / 14)
+        c.jaws = inputs.jaws_square(n_cp, 2.37 * px, 2.37 * px)
+        eng = E.DoseEngine(c, conv=conv)
+        p, w, best = (_t(c.leaves), _t(c.jaws), _t(c.mu)), torch.ones(c.shape, device="cuda"), float("inf")
+        for _ in range(8):
+            E.profile_begin(64)
+            eng.backward(*p, w)
+            best = min(best, E.profile_end()["conv_mfma_f32_adj" if conv == "fp32" else "conv_mfma_bf16_adj"][1])
+        _say("%s adjoint, %d control points of %d x %d: %.4f ms" % (conv, n_cp, 2 * px + 1, 2 * px + 1, best))
+        ms[px] = best
+    assert ms[32] <= most * ms[20]
