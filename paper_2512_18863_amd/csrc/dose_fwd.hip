@@ -556,13 +556,15 @@ __global__ void k_fill_zero(size_t n, T* __restrict__ p) {
 
 // Rays of a control point to be marched: those of the largest jaw rectangle the field
 // limit allows (the plane minus the kernel halo), widened by the fluence corrections;
-// without a box the whole plane.  Workgroups walk them grid-stride, so a larger
-// rectangle (jaws beyond the field limit) is still covered.
+// without a box the whole plane.  `margin`: pixels on each side more, for the grid (a
+// turned rectangle has two, and a workgroup left over costs less than a second round;
+// the walk is grid-stride, so that larger rectangles, from jaws beyond the field limit,
+// are covered all the same).
 template <typename T>
-int march_rays(const Geo<T>& g, const int* box) {
+int march_rays(const Geo<T>& g, const int* box, int margin) {
   if (!box) return g.Nu * g.Nv;
-  const int du = g.fcorr ? g.conv_du : 0, dv = g.fcorr ? g.conv_dv : 0;
-  return max(1, min(g.Nu, g.Nu - 2 * (g.h - du))) * max(1, min(g.Nv, g.Nv - 2 * (g.h - dv)));
+  const int du = margin - g.h + (g.fcorr ? g.conv_du : 0), dv = margin - g.h + (g.fcorr ? g.conv_dv : 0);
+  return max(1, min(g.Nu, g.Nu + 2 * du)) * max(1, min(g.Nv, g.Nv + 2 * dv));
 }
 
 // The scan's wavefronts per workgroup: segments of at most MARCH_SEG planes where
@@ -570,7 +572,7 @@ int march_rays(const Geo<T>& g, const int* box) {
 template <typename T, int MODE, typename E>
 hipError_t launch_march_mode(const Geo<T>& g, int nb, const T* frame, const T* rho_t, const T* F, const T* z,
                              const T* dd, E* vol, T* A, hipStream_t s, const int* box) {
-  const int rays = march_rays(g, box);
+  const int rays = march_rays(g, box, 3);
   const dim3 serial((rays + 255) / 256, nb);
   if (g.march_scan == MARCH_SERIAL) {
     hipLaunchKernelGGL((k_march_serial<T, MODE, E, false>), serial, dim3(256), g.n_dd * sizeof(T), s, g, frame, rho_t,
@@ -580,7 +582,7 @@ hipError_t launch_march_mode(const Geo<T>& g, int nb, const T* frame, const T* r
   // Geometry cache of 60 control points of 89 x 89 x 183 nodes: 0.31 ms (scan 0.58); the march
   // and its adjoint of 90 with fluence corrections (n = 31, 59 x 59): 0.21 + 0.31 ms (scan
   // 0.39 + 0.57).  The same bits.
-  if (g.march_scan == MARCH_SEGMENTS && !march_scan_wins((long)(rays + 63) / 64 * nb, g.Nk)) {
+  if (g.march_scan == MARCH_SEGMENTS && !march_scan_wins((long)(march_rays(g, box, 0) + 63) / 64 * nb, g.Nk)) {
     hipLaunchKernelGGL((k_march_serial<T, MODE, E, true>), serial, dim3(256), g.n_dd * sizeof(T), s, g, frame, rho_t,
                        F, z, dd, vol, A, box);
     return hipGetLastError();
