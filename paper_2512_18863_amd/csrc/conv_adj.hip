@@ -226,20 +226,22 @@ __global__ void __launch_bounds__(512, T <= 2 ? 5 : T == 3 ? 4 : 2) k_conv_adj(G
   }
 }
 
-// Wavefronts of a workgroup and its LDS for pieces of n x n tiles.
-int adj_waves(int np, int n, int h) { return h <= 16 || (n == 4 && (np == 1 || h <= 24)) ? 4 : 8; }
+// LDS of a workgroup for pieces of n x n tiles, and its wavefronts: four for small
+// kernels and for pieces of four where two workgroups fit a compute unit.
 int adj_pitch(const Geo<float>& g, int n) { return (min(g.Nv, 16 * n + 2 * g.h) + 31) / 32 * 32 + 8; }
 size_t adj_lds(const Geo<float>& g, int np, int n) {
-  const size_t img = sizeof(float) * (size_t)adj_img_rows(n, g.h) * adj_pitch(g, n);
-  const size_t red = (size_t)adj_waves(np, n, g.h) * n * 1024;
+  const size_t img = sizeof(float) * (size_t)adj_img_rows(n, g.h) * adj_pitch(g, n), red = (size_t)8 * n * 1024;
   return sizeof(unsigned) * (size_t)reg_tap_words(g.h, np) + (img > red ? img : red);
 }
+bool adj_two_fit(const Geo<float>& g, int np, int n) { return adj_lds(g, np, n) <= 80 * 1024; }
+int adj_waves(const Geo<float>& g, int np, int n) { return g.h <= 16 || (n == 4 && adj_two_fit(g, np, n)) ? 4 : 8; }
 
 // Tiles per side of a piece for rectangles of side `side` pixels: one piece up to three
 // tiles; above, the least of column groups over all pieces x time of a (group, tap row)
-// pair, measured relative to pieces of two: three 1.6 and four 3.0 (BF16: 1.5, 2.2),
-// pieces that are a tile smaller than their kernel 0.8 (0.7) of that, and 1.5 where FP32
-// windows of two or three leave one workgroup to a compute unit.  FP32, 75 planes each:
+// pair, measured relative to pieces of two: three 1.45 and four 2.8 (BF16: 1.2, 1.6),
+// pieces that are a tile smaller than their kernel 0.9 (0.75) of that, and where FP32
+// windows leave one workgroup to a compute unit 1.75 (pieces of four, which have few
+// wavefronts anyway, 1.2).  FP32, 75 planes each:
 //   60 control points, n = 13, 57 x 57 pixels  0.136 ms in pieces of 2, 0.164 of 3, 0.156 of 4
 //   20, n = 13, 121 x 121                      0.168, 0.148, 0.191
 //   60, n = 45, 57 x 57                        0.53, 0.58, 0.46
@@ -248,7 +250,7 @@ size_t adj_lds(const Geo<float>& g, int np, int n) {
 int adj_tiles(const Geo<float>& g, int np, double side) {
   const int blocks = (int)ceil(side / 16.0);
   if (blocks <= 3) return blocks > 1 ? blocks : 1;
-  const double pair[5] = {0.0, 0.0, 1.0, np == 3 ? 1.6 : 1.5, np == 3 ? 3.0 : 2.2};
+  const double pair[5] = {0.0, 0.0, 1.0, np == 3 ? 1.45 : 1.2, np == 3 ? 2.8 : 1.6};
   const double c0 = 0.5 * (g.Nv - side);  // the rectangle's first column
   int best = 2;
   double least = 1e30;
@@ -261,8 +263,8 @@ int adj_tiles(const Geo<float>& g, int np, double side) {
       groups += fmax(1.0, ceil((b - a) / 32.0 - 1e-9));
     }
     double cost = m * groups * pair[n];
-    if (tiles < n) cost *= np == 3 ? 0.8 : 0.7;
-    if (np == 3 && n < 4 && adj_lds(g, np, n) > 80 * 1024) cost *= 1.5;
+    if (tiles < n) cost *= np == 3 ? 0.9 : 0.75;
+    if (np == 3 && !adj_two_fit(g, np, n)) cost *= n < 4 ? 1.75 : 1.2;
     if (cost < least) {
       least = cost;
       best = n;
@@ -283,7 +285,7 @@ hipError_t launch_adj_cfg(const Geo<float>& g, int nb, int pieces, const int4* b
   }
   const long n_items = (long)nb * g.Nk;
   if (n_items > 0x7fffffffL) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k_conv_adj<NP, N, N>), dim3((unsigned)n_items, pieces), dim3(64 * adj_waves(NP, N, g.h)), lds, s, g,
+  hipLaunchKernelGGL((k_conv_adj<NP, N, N>), dim3((unsigned)n_items, pieces), dim3(64 * adj_waves(g, NP, N)), lds, s, g,
                      adj_pitch(g, N), box, z, in, out);
   return hipGetLastError();
 }
@@ -298,8 +300,9 @@ hipError_t launch_adj_np(const Geo<float>& g, int nb, const int4* box, const flo
   const int half_u = (g.Nu - 1) / 2 - g.h, half_v = (g.Nv - 1) / 2 - g.h;  // field limit in pixels
   const int fu = 2 * (half_u > 0 ? half_u : 0) + 1, fv = 2 * (half_v > 0 ? half_v : 0) + 1;
   const int br = min(g.Nu, fu + 2 * g.conv_du), bc = min(g.Nv, fv + 2 * g.conv_dv);
-  const double turned = g.conv_du == g.box_du && g.conv_dv == g.box_dv ? 1.0 : 0.7;
-  const double ur = fmin(g.Nu, 0.95 * fu + 2 * turned * g.conv_du), uc = fmin(g.Nv, 0.95 * fv + 2 * turned * g.conv_dv);
+  const bool turned = g.conv_du != g.box_du || g.conv_dv != g.box_dv;
+  const double open = turned ? 0.9 : 0.95, wide = turned ? 1.4 : 2.0;
+  const double ur = fmin(g.Nu, open * fu + wide * g.conv_du), uc = fmin(g.Nv, open * fv + wide * g.conv_dv);
   const int n = adj_tiles(g, NP, fmax(ur, uc));
   const int pieces = ((br + 16 * n - 1) / (16 * n)) * ((bc + 16 * n - 1) / (16 * n));
   switch (n) {
