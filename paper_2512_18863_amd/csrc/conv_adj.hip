@@ -190,13 +190,21 @@ __global__ void __launch_bounds__(512, T <= 2 ? 5 : T == 3 ? 4 : 2) k_conv_adj(G
         }
       }
     };
-    // a rectangle (or its last piece) one row or column of tiles smaller leaves them out
+    // a rectangle (or its last piece) one row or column of tiles smaller leaves them out,
+    // and one of an opening far inside the field limits takes the least square that holds it
     typedef std::integral_constant<int, T> FT;
     typedef std::integral_constant<int, (T > 1 ? T - 1 : 1)> ST;
     typedef std::integral_constant<int, CB> FC;
     typedef std::integral_constant<int, (CB > 1 ? CB - 1 : 1)> SC;
+    typedef std::integral_constant<int, 1> One;
+    typedef std::integral_constant<int, 2> Two;
     const bool st = I1 - I <= 16 * (T - 1), sc = J1 - J <= 16 * (CB - 1);
-    if (st) {
+    const int side = max(I1 - I, J1 - J);
+    if (T > 2 && side <= 16) {
+      products(One(), One());
+    } else if (T > 3 && side <= 32) {
+      products(Two(), Two());
+    } else if (st) {
       if (sc) products(ST(), SC());
       else products(ST(), FC());
     } else {
