@@ -384,8 +384,30 @@ __device__ __forceinline__ void march_ray_segments(const Geo<T>& g, int b, int i
   if (MODE == MARCH_ADJOINT) A[(size_t)b * plane + r] = total + acc;
 }
 
-// Without a box, one thread per ray of the plane; with a box, the block row
-// blockIdx.y = b walks only the rays of control point b's rectangle (grid-stride),
+// Workgroups of a march: block q of n of control point b.  Fluence corrections widen the
+// largest rectangle, and with it the grid, by up to the blur's radius, and openings are
+// often much smaller, so that half of the workgroups have none.  Control points then run
+// fastest, and those workgroups come last: with rays fastest they fell on the same compute
+// units for every control point and left those idle (60 of 31 x 33 rays and 99 planes in a
+// grid of 45 x 45, march and adjoint as a scan: 0.069 + 0.083 ms, now 0.043 + 0.053).
+// Uncorrected plans keep rays fastest (60 openings of 24 x 24 mm in 120 mm limits, march:
+// 0.053 ms, 0.056 with control points fastest).
+template <typename T>
+__host__ __device__ bool march_cp_first(const Geo<T>& g, const int* box) {
+  return box && g.fcorr;
+}
+
+struct MarchBlock {
+  int b, q, n;
+  template <typename T>
+  __device__ MarchBlock(const Geo<T>& g, const int* box) {
+    const bool cf = march_cp_first(g, box);
+    b = cf ? blockIdx.x : blockIdx.y, q = cf ? blockIdx.y : blockIdx.x, n = cf ? gridDim.y : gridDim.x;
+  }
+};
+
+// Without a box, one thread per ray of the plane; with a box, the blocks of control
+// point b walk only the rays of control point b's rectangle (grid-stride),
 // so no lanes idle on rays outside it.  (In adjoint mode A outside the box is
 // cleared beforehand.)  SEG: the scan's order.
 template <typename T, int MODE, typename E, bool SEG>
@@ -397,7 +419,8 @@ __global__ void __launch_bounds__(256) k_march_serial(Geo<T> g, const T* __restr
   T* tab = reinterpret_cast<T*>(smem_raw);
   for (int q = threadIdx.x; q < g.n_dd; q += 256) tab[q] = dd[q];
   __syncthreads();
-  const int b = blockIdx.y;
+  const MarchBlock mb(g, box);
+  const int b = mb.b;
   auto march = [&](int i, int j) {
     if constexpr (SEG) march_ray_segments<T, MODE, E>(g, b, i, j, frame, rho_t, F, zca, tab, vol, A);
     else march_ray<T, MODE, E>(g, b, i, j, frame, rho_t, F, zca, tab, vol, A);
@@ -405,12 +428,12 @@ __global__ void __launch_bounds__(256) k_march_serial(Geo<T> g, const T* __restr
   if (box) {
     const int* bx = box + 4 * b;
     const int bw = bx[3] - bx[2], area = bx[1] > bx[0] && bw > 0 ? (bx[1] - bx[0]) * bw : 0;
-    for (int rr = blockIdx.x * 256 + threadIdx.x; rr < area; rr += gridDim.x * 256) {
+    for (int rr = mb.q * 256 + threadIdx.x; rr < area; rr += mb.n * 256) {
       const int li = rr / bw;
       march(bx[0] + li, bx[2] + rr - li * bw);
     }
   } else {
-    const int r = blockIdx.x * 256 + threadIdx.x;
+    const int r = mb.q * 256 + threadIdx.x;
     if (r < g.Nu * g.Nv) march(r / g.Nv, r % g.Nv);
   }
 }
@@ -449,7 +472,8 @@ __global__ void __launch_bounds__(64 * MARCH_MAXW) k_march_scan(Geo<T> g, const 
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   for (int q = tid; q < g.n_dd; q += blockDim.x) tab[q] = dd[q];
   __syncthreads();
-  const int b = blockIdx.y;
+  const MarchBlock mb(g, box);
+  const int b = mb.b;
   const int plane = g.Nu * g.Nv;
   int u0 = 0, nu = g.Nu, v0 = 0, nv = g.Nv;
   if (box) {
@@ -463,7 +487,7 @@ __global__ void __launch_bounds__(64 * MARCH_MAXW) k_march_scan(Geo<T> g, const 
   const bool keep = ke - kb <= MARCH_SEG;  // one pass holds the whole segment
   const T sn = frame[2 * b], cs = frame[2 * b + 1];
   const T* zb = zca + (size_t)b * g.Nk;
-  for (int grp = blockIdx.x; grp * 64 < area; grp += gridDim.x) {
+  for (int grp = mb.q; grp * 64 < area; grp += mb.n) {
     const int rr = grp * 64 + lane;
     const bool valid = rr < area;
     const int li = valid ? rr / nv : 0;
@@ -573,7 +597,10 @@ template <typename T, int MODE, typename E>
 hipError_t launch_march_mode(const Geo<T>& g, int nb, const T* frame, const T* rho_t, const T* F, const T* z,
                              const T* dd, E* vol, T* A, hipStream_t s, const int* box) {
   const int rays = march_rays(g, box, 3);
-  const dim3 serial((rays + 255) / 256, nb);
+  const auto grid_of = [&](int blocks) {
+    return march_cp_first(g, box) ? dim3(nb, min(blocks, 65535)) : dim3(blocks, nb);
+  };
+  const dim3 serial = grid_of((rays + 255) / 256);
   if (g.march_scan == MARCH_SERIAL) {
     hipLaunchKernelGGL((k_march_serial<T, MODE, E, false>), serial, dim3(256), g.n_dd * sizeof(T), s, g, frame, rho_t,
                        F, z, dd, vol, A, box);
@@ -582,7 +609,12 @@ hipError_t launch_march_mode(const Geo<T>& g, int nb, const T* frame, const T* r
   // Geometry cache of 60 control points of 89 x 89 x 183 nodes: 0.31 ms (scan 0.58); the march
   // and its adjoint of 90 with fluence corrections (n = 31, 59 x 59): 0.21 + 0.31 ms (scan
   // 0.39 + 0.57).  The same bits.
-  if (g.march_scan == MARCH_SEGMENTS && !march_scan_wins((long)(march_rays(g, box, 0) + 63) / 64 * nb, g.Nk)) {
+  // With boxes only the rays of the largest rectangle are known here, and openings often hold
+  // half of them or less: counted as half (12 control points of 24 x 24 mm openings in
+  // 120 mm limits, corrected and turned, n = 61 at 5 mm: 0.038 + 0.049 ms as a scan, 0.050 +
+  // 0.073 by threads).
+  const long waves = (long)(march_rays(g, box, 0) + 63) / 64 * nb / (box ? 2 : 1);
+  if (g.march_scan == MARCH_SEGMENTS && !march_scan_wins(waves, g.Nk)) {
     hipLaunchKernelGGL((k_march_serial<T, MODE, E, true>), serial, dim3(256), g.n_dd * sizeof(T), s, g, frame, rho_t,
                        F, z, dd, vol, A, box);
     return hipGetLastError();
@@ -590,7 +622,7 @@ hipError_t launch_march_mode(const Geo<T>& g, int nb, const T* frame, const T* r
   const int nw = march_segments(g.Nk);
   const size_t lds = sizeof(T) * (2 * MARCH_MAXW * 64 + (size_t)g.n_dd);
   if (lds > 64 * 1024) return hipErrorInvalidConfiguration;
-  const dim3 grid((rays + 63) / 64, nb);
+  const dim3 grid = grid_of((rays + 63) / 64);
   hipLaunchKernelGGL((k_march_scan<T, MODE, E>), grid, dim3(64 * nw), lds, s, g, frame, rho_t, F, z, dd, vol, A,
                      box);
   return hipGetLastError();
