@@ -599,22 +599,22 @@ static hipError_t launch_bf16_adj_win_nk(const Geo<float>& g, int nb, const int4
   return hipGetLastError();
 }
 
-// The windowed adjoint for K-step counts up to 4 (h <= 48); false: not served.
+// The windowed adjoint for K-step counts up to 4 (h <= 48); false: not served.  (Kernels of
+// h = 1 to 16, two K-steps, never come here: launch_conv_mfma_bf16.)
 static bool launch_bf16_adj_win(const Geo<float>& g, int nb, const int4* box, const float* z, const float* in,
                                 float* out, hipStream_t s, hipError_t* err) {
   const int nk = (32 + 2 * g.h + 31) / 32;
   switch (nk) {
     case 1: *err = launch_bf16_adj_win_nk<1>(g, nb, box, z, in, out, s); return true;
-    case 2: *err = launch_bf16_adj_win_nk<2>(g, nb, box, z, in, out, s); return true;
     case 3: *err = launch_bf16_adj_win_nk<3>(g, nb, box, z, in, out, s); return true;
     case 4: *err = launch_bf16_adj_win_nk<4>(g, nb, box, z, in, out, s); return true;
     default: return false;
   }
 }
 
-// Bounds of the aperture rectangle for jaws inside the field limits, as the
-// aperture-box kernel computes it (one pixel of margin each side): the image is
-// sized for it, and larger rectangles are processed in row and column chunks.
+// Extent of the aperture rectangle for jaws inside the field limits, with one pixel on each
+// side to spare (the aperture-box kernel adds none): the image is sized for it, and larger
+// rectangles are processed in row and column chunks.
 static int box_extent(double F, double D, double c, int N) {
   const double fa = -F / D + c - 0.5, fb = F / D + c + 0.5;
   int lo = (int)std::floor(fa) - 1, hi = (int)std::ceil(fb) + 1;

@@ -1184,8 +1184,8 @@ static hipError_t launch_f32_adj_win_cfg(const Geo<float>& g, const AdjWin& aw, 
   return hipGetLastError();
 }
 
-// Pieces sized for the largest rectangle that jaws inside the field limits give
-// (bigger rectangles take several pieces), at most 16 tiles (two per wavefront),
+// Pieces sized for the largest rectangle that jaws inside the field limits give, 2 half + 1
+// pixels, and three to spare (bigger rectangles take several pieces), at most 16 tiles (two per wavefront),
 // made smaller while the image does not fit the LDS.  False: not even one tile's
 // image fits.
 static bool f32_adj_win_shape(const Geo<float>& g, AdjWin* out) {
