@@ -26,6 +26,8 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 PEAK_FP32_MFMA_TFLOPS = 157.3     # MI355X dense FP32 matrix peak
 PEAK_BF16_MFMA_TFLOPS = 2500.0    # MI355X dense BF16 matrix peak
+SPLIT_PRODUCTS = 6                # BF16 products per FP32 product where the convolutions split FP32 operands
+SPLIT_MAX_TAPS = 63               # widest kernel for which they do
 PEAK_HBM_GBS = 8000.0
 
 
@@ -159,6 +161,7 @@ class Work:
     def __init__(self, case, eng):
         import numpy as np
         n = eng.spec.n_taps
+        self.n_taps = n
         self.n_cp = case.n_cp
         self.nodes = case.n_cp * eng.Nk * eng.Nu * eng.Nv
         self.ap_nodes = int(aperture_pixels(case.jaws, case.lat_step, eng.Nu, eng.Nv).sum()) * eng.Nk
@@ -178,7 +181,9 @@ class Work:
         if kernel in hbm:
             return "hbm", float(hbm[kernel]), PEAK_HBM_GBS, "GB/s"
         if kernel.startswith("conv_mfma_f32"):
-            return "mfma", self.conv_flops, PEAK_FP32_MFMA_TFLOPS, "TFLOP/s"
+            # the unit the kernels run on: BF16 matrix instructions, six products per FP32 one
+            peak = PEAK_BF16_MFMA_TFLOPS / SPLIT_PRODUCTS if self.n_taps <= SPLIT_MAX_TAPS else PEAK_FP32_MFMA_TFLOPS
+            return "mfma", self.conv_flops, round(peak, 1), "TFLOP/s"
         if kernel.startswith("conv_mfma_bf16"):
             return "mfma", self.conv_flops, PEAK_BF16_MFMA_TFLOPS, "TFLOP/s"
         return None

@@ -450,7 +450,6 @@ int forward_impl(const pdrt_grid* grid, const T* rho, const pdrt_beam* beam, con
   const bool rot = beam->collimator_deg != nullptr;
   T* cframe = (T*)(w + P.lay.cframe);
   T* Fb = rot ? (T*)(w + P.lay.rot) : F;
-  // the corrections spread the aperture's fluence by their blur radii
   // rays outside the box are skipped only when the convolution reads just the box
   const int* ray_box = conv_uses_box<T>(g, spec->conv_mode) ? box : nullptr;
   const T* dd = (const T*)spec->dd;
@@ -526,8 +525,6 @@ int backward_impl(const pdrt_grid* grid, const T* rho, const pdrt_beam* beam, co
   const bool rot = beam->collimator_deg != nullptr;
   T* cframe = (T*)(w + P.lay.cframe);
   T* Ab = rot ? (T*)(w + P.lay.rot) : A;
-  // the parameter gradients read A inside the aperture rectangle; the corrections'
-  // adjoint gathers it from as far as their blur radii
   // with a box-restricted convolution H is valid only inside the box
   const int* ray_box = conv_uses_box<T>(g, spec->conv_mode) ? box : nullptr;
   const T* dd = (const T*)spec->dd;

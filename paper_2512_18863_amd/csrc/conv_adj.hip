@@ -10,13 +10,15 @@
 //   A[m][k] = K[p][c_k - j_m] (from the extended tap row), B[k][n] = S_p[i_n][c_k].
 // The window of plane rows and columns that a piece of T x CB output tiles reads sits
 // in LDS in FP32; a wavefront forms S_p in FP32 and splits it, like the taps, exactly
-// into three BF16 pieces (see conv_fwd_reg.hip: six piece products per product, each
-// exact, FP32 sums).  Folding the two rows first halves the matrix work; the split is
+// into three BF16 pieces (conv_fwd_reg.hip: six exact piece products per product, what is
+// left out, FP32 sums; error of the output against FP64 on the 128^3 plan 7.1e-7 on FP32
+// matrix instructions, 1.6e-7 now, with fluence corrections and collimator rotation 9.9e-7
+// and 2.6e-7).  Folding the two rows first halves the matrix work; the split is
 // done in the vector unit, which the matrix instructions leave free.
 //
 // One workgroup per (control point, plane) item and piece; a rectangle's pieces have equal
-// numbers of tiles.  Its wavefronts share the (column group, tap row) pairs evenly, each for all T x CB tiles, so a split feeds CB
-// tiles and a tap run T.  Their sums are added in LDS in wavefront order, one row of
+// numbers of tiles.  Its wavefronts share the (column group, tap row) pairs evenly, each
+// for all T x CB tiles, so a split feeds CB tiles and a tap run T.  Their sums are added in LDS in wavefront order, one row of
 // tiles at a time.  (Wavefronts come in multiples of four: a workgroup of six, two on
 // two of the SIMDs, kept a second one off the compute unit.)
 //
@@ -27,11 +29,11 @@
 // What bounds it: vector instructions, 52 per S_p fragment beside 12 to 24 matrix
 // instructions of 16 cycles.  FP32 against the windowed kernel on FP32 matrix
 // instructions (conv_mfma.hip, which remains for h > 31): 180 control points at 128^3 (n
-// = 61, 27 x 27 outputs) 1.33 ms (1.61), at 224 x 224 x 105 (n = 55, 41 x 41) 3.3 ms
-// (5.8), at 192 x 192 x 128 (n = 31) 0.90 ms (1.15), 90 at 128 x 128 x 96 (n = 15) 0.13 ms
-// (0.22); 90 with fluence corrections and collimator rotation (up to 99 x 99) 7.0 ms
-// (9.1 by regions).  BF16: 1.8 ms on the second (2.9), 0.086 on the fourth (0.14), 3.8
-// on the last (13).
+// = 61, 27 x 27 outputs) 1.34 to 1.39 ms by clock (1.61), at 224 x 224 x 105 (n = 55, 41 x
+// 41) 3.5 ms (5.8), at 192 x 192 x 128 (n = 31) 0.88 ms (1.15), 90 at 128 x 128 x 96 (n =
+// 15) 0.13 ms (0.22); 90 with fluence corrections and collimator rotation (up to 99 x 99)
+// 6.5 ms (9.1 by regions).  BF16: 1.8 ms on the second (2.9), 0.086 on the fourth (0.14),
+// 3.8 on the last (13).
 #include <type_traits>
 
 #include "conv_common.hpp"
@@ -119,9 +121,10 @@ __global__ void __launch_bounds__(512, T <= 2 ? 5 : T == 3 ? 4 : 2) k_conv_adj(G
       for (int gq = ua / h1; gq * h1 < uz; ++gq) {
         const int pa = max(ua - gq * h1, 0), pz = min(uz - gq * h1, h1);
         // tap runs of the lane: four taps each for columns 4 kk and 16 + 4 kk of the group, a
-        // run that meets no tap moved to the zeros beside them.  (Word offsets into the rows, not
-        // pointers: pointers kept in an array lost their address space with one column of
-        // tiles, and generic loads took the place of LDS reads, 0.57 against 0.19 ms for 90 control points of 98 planes, n = 61.)
+        // run that meets no tap moved to the zeros beside them.  (Word offsets into the rows,
+        // not pointers: pointers kept in an array lost their address space with one column of
+        // tiles, and generic loads took the place of LDS reads, 0.57 against 0.20 ms for 90
+        // control points of 98 planes, n = 61.)
         int run[CC][2];
 #pragma unroll
         for (int c = 0; c < CC; ++c)

@@ -249,9 +249,9 @@ __device__ __forceinline__ void put_win(const float* __restrict__ src, const Geo
 constexpr int kRegMaxH = 31;  // widest kernel half-width served
 
 // BF16 tap rows (FP32 taps as three BF16 pieces).  Element x of extended tap row p holds
-// K[p][|x - kRegOff|] for |x - kRegOff| <= h, else 0.  Each lane reads a run of eight taps; a run wholly left or right of the taps is
-// moved to the nearest run of zeros that starts with its parity (two margins of nine
-// elements hold them).  A row is two copies of BF16 pairs, the second shifted by one
+// K[p][|x - kRegOff|] for |x - kRegOff| <= h, else 0.  Each lane reads a run of eight taps
+// (the adjoint two of four); a run wholly left or right of the taps is moved to the nearest
+// run of zeros that starts with its parity (margins of nine elements hold them).  A row is two copies of BF16 pairs, the second shifted by one
 // tap, so that every run is four aligned words.  Rows have the length of the widest
 // kernel served, so that a lane's reads of one row are one address and constant
 // offsets: copy c, row p, piece i starts at word ((c (h + 1) + p) NP + i) kRegW.
@@ -259,7 +259,8 @@ constexpr int kRegOff = kRegMaxH + 9;
 constexpr int kRegW = (kRegOff + kRegMaxH + 10 + 1) / 2;
 
 // The NP BF16 pieces of a pair, packed (a in the low half-words): piece i is the rounded
-// remainder of the ones before, so three of them hold an FP32 number exactly.
+// remainder of the ones before, so three of them hold an FP32 number of 2^-109 or more
+// exactly.
 typedef __bf16 bf16x2_c __attribute__((ext_vector_type(2)));
 typedef float f32x2_c __attribute__((ext_vector_type(2)));
 template <int NP>

@@ -17,12 +17,19 @@
 // FP32 operands are split exactly into three BF16 pieces, x = x0 + x1 + x2 (each the
 // rounded remainder of the ones before: 8 significant bits and a sign each, 24 in
 // all), and a product takes the six piece products down to x0 y2, x2 y0 and x1 y1,
-// smallest first, every one exact in the FP32 accumulator; the three left out are
-// below 2^-26 of the product.  Six BF16 instructions of K = 32 take 96 cycles where
-// the eight FP32 instructions of K = 4 take 256, and eight times fewer roundings
-// enter a sum: the dose's error against FP64 went from 1.4e-7 to 1.3e-7 on the 128^3
-// plan and from 4.9e-6 to 6.6e-7 with fluence corrections and collimator rotation.
-// A non-finite input makes every output its column group reaches non-finite.
+// smallest first, every product exact, the sums in FP32.  Of the three left out, x1 y2
+// and x2 y1 are up to 2^-25 of the product each and x2 y2 2^-34: 2^-24 together at most,
+// the rounding of one FP32 product, and 2^-27.5 in the root mean square.  Six BF16
+// instructions of K = 32 take 96 cycles where the eight FP32 instructions of K = 4 take
+// 256, and fewer roundings enter a sum (an instruction rounds four times).  Error of the
+// convolution's output against FP64, root mean square over that of the output, FP32
+// instructions -> six products: 128^3 plan 1.51e-7 -> 1.40e-7, with fluence corrections
+// and collimator rotation 5.2e-6 -> 3.0e-7.  (The dose, which rounds in other steps too:
+// 1.41e-7 -> 1.50e-7 on the plan.)  The third piece of a number below about 2^-109 is
+// subnormal and lost: such operands keep 16 bits or fewer (a loss scaled by 1e-36 has its
+// gradients within 2.8e-6 in place of 3.4e-7).  A non-finite input makes outputs
+// non-finite as far as its column group is multiplied: the strips that the group reaches,
+// and for the first group of a box of one chunk every strip.
 //
 // The product's box rows lie along the lanes of each 16-lane row of the result, so
 // moving it by p rows is a DPP row shift within those 16 lanes: the part that stays
@@ -55,9 +62,10 @@
 // What bounds it: the vector instructions of the row shifts (16 per product) beside
 // the matrix instructions (the two overlap: 16 cycles of matrix unit and about 7 of
 // issue per product).  180 control points at 128^3 (n = 61, 27 x 27 boxes, 32940
-// planes): FP32 0.92 ms (1.91 on FP32 matrix instructions), BF16 0.53 ms (0.65); 224 x
-// 224 x 105 (n = 55, 41 x 41): 3.0 ms (6.3); 90 control points with fluence corrections
-// and collimator rotation (n = 61, up to 99 x 99): 6.1 ms (24.9).
+// planes): FP32 0.94 to 1.02 ms by clock (1.91 on FP32 matrix instructions), BF16 0.53 ms
+// (0.65); 224 x 224 x 105 (n = 55, 41 x 41): 3.2 ms (6.3); 90 control points with fluence
+// corrections and collimator rotation (n = 61, up to 99 x 99): 4.9 ms (24.9; 6.1 with every
+// column group loaded for every strip and strips added by atomics).
 #include "conv_common.hpp"
 
 namespace pdrt {
@@ -380,7 +388,8 @@ static hipError_t launch_reg_cfg(const Geo<float>& g, int nb, const int4* box, c
   // ms); else two for the short loops of small kernels (90 control points, n = 15: 0.095
   // against 0.117 ms), four for larger ones (180, n = 61: 1.07 against 1.26 ms)
   const int nw = n_items <= 2 * device_cus() ? 8 : g.h <= 16 ? 2 : 4;
-  hipLaunchKernelGGL((k_conv_fwd_reg<NP, T, SU, CARRY>), dim3((unsigned)n_items), dim3(64 * nw), lds, s, g, box, z, in, out);
+  hipLaunchKernelGGL((k_conv_fwd_reg<NP, T, SU, CARRY>), dim3((unsigned)n_items), dim3(64 * nw), lds, s, g, box, z, in,
+                     out);
   return hipGetLastError();
 }
 

@@ -159,8 +159,8 @@ class Net3D:
         self.stats = torch.empty(2, **f32)
         self.loss = torch.empty(1, **f32)
         # weight-gradient splits per level: a workgroup each, walking tiles of 128 positions.  4096, 2048 and
-        # 1024 positions per split and at least 64 splits keep the 256 compute units busy on the small levels
-        # too (128^3, all ten layers: 1.3 ms; with 4096 positions on every level 1.9 ms)
+        # 1024 positions per split, and 64 splits where a level has that many tiles, keep the 256 compute units
+        # busy on the small levels too (128^3, all ten layers: 1.3 ms; with 4096 positions on every level 1.9 ms)
         self.nsplit = [max(1, min(n // 128, 64), n // (4096 >> lvl)) for lvl, n in enumerate(self.npos)]
         wsz = max(lib.pdrt_conv3d_wgrad_ws_bytes(cout, c1 + c2, self.nsplit[lvl]) for (_, c1, c2, cout, lvl) in LAYERS)
         wsz = max(wsz, lib.pdrt_net_head_ws_bytes(n0, HEAD_C), lib.pdrt_net_loss_ws_bytes(n0),
