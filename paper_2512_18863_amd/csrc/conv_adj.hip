@@ -247,35 +247,45 @@ size_t adj_lds(const Geo<float>& g, int np, int n) {
 bool adj_two_fit(const Geo<float>& g, int np, int n) { return adj_lds(g, np, n) <= 80 * 1024; }
 int adj_waves(const Geo<float>& g, int np, int n) { return g.h <= 16 || (n == 4 && adj_two_fit(g, np, n)) ? 4 : 8; }
 
-// Tiles per side of a piece for rectangles of side `side` pixels: one piece up to three
-// tiles; above, the least of column groups over all pieces x time of a (group, tap row)
-// pair, measured relative to pieces of two: three 1.45 and four 2.8 (BF16: 1.2, 1.6),
-// pieces that are a tile smaller than their kernel 0.9 (0.75) of that, and where FP32
-// windows leave one workgroup to a compute unit 1.75 (pieces of four, which have few
-// wavefronts anyway, 1.2).  FP32, 75 planes each:
+// Estimated time of a rectangle of side `side` pixels in pieces of n x n tiles: column
+// groups over all pieces x time of a (group, tap row) pair, measured relative to pieces of
+// two: three 1.45 and four 2.8 (BF16: 1.2, 1.6), pieces that are a tile smaller than their
+// kernel 0.7 of that (BF16: three 0.8, four 0.9), and where FP32 windows leave one workgroup
+// to a compute unit 1.75 (pieces of four, which have few wavefronts anyway, 1.1).
+double adj_cost(const Geo<float>& g, int np, int n, double side) {
+  const int blocks = max(1, (int)ceil(side / 16.0)), m = (blocks + n - 1) / n, tiles = (blocks + m - 1) / m;
+  const double c0 = 0.5 * (g.Nv - side);  // the rectangle's first column
+  double groups = 0.0;
+  for (int j = 0; j < m; ++j) {
+    const double a = fmax(0.0, c0 + 16 * tiles * j - g.h);
+    const double b = fmin(g.Nv, fmin(c0 + 16 * tiles * (j + 1), c0 + side) + g.h);
+    groups += fmax(1.0, ceil((b - a) / 32.0 - 1e-9));
+  }
+  const double pair[5] = {0.0, 0.0, 1.0, np == 3 ? 1.45 : 1.2, np == 3 ? 2.8 : 1.6};
+  double cost = m * groups * pair[n];
+  if (tiles < n) cost *= np == 3 ? 0.7 : n < 4 ? 0.8 : 0.9;
+  if (np == 3 && !adj_two_fit(g, np, n)) cost *= n < 4 ? 1.75 : 1.1;
+  return cost;
+}
+
+// Tiles per side of a piece for rectangles that are usually of side `usual` and at most
+// `most` pixels: one piece up to three tiles; above, the least of both sides' times (a
+// rectangle at the limits may take a row of tiles more, and with it more pieces), weighed
+// as fits best 650 shapes of 13 to 61 taps and 7 to 97 pixels with and without corrections
+// and rotation, openings at the limits and up to a tenth inside: 1 : 0.7, BF16 1 : 2.  FP32,
+// 75 planes each:
 //   60 control points, n = 13, 57 x 57 pixels  0.136 ms in pieces of 2, 0.164 of 3, 0.156 of 4
 //   20, n = 13, 121 x 121                      0.168, 0.148, 0.191
 //   60, n = 45, 57 x 57                        0.53, 0.58, 0.46
 //   60, n = 61, 57 x 57                        0.66, 1.03, 0.76
 //   40, n = 55, 103 x 103 (corrections)        1.24, 1.74, 1.17
-int adj_tiles(const Geo<float>& g, int np, double side) {
-  const int blocks = (int)ceil(side / 16.0);
-  if (blocks <= 3) return blocks > 1 ? blocks : 1;
-  const double pair[5] = {0.0, 0.0, 1.0, np == 3 ? 1.45 : 1.2, np == 3 ? 2.8 : 1.6};
-  const double c0 = 0.5 * (g.Nv - side);  // the rectangle's first column
+int adj_tiles(const Geo<float>& g, int np, double usual, double most) {
+  const int blocks = (int)ceil(most / 16.0);
+  if (blocks <= 3) return max(1, blocks);
   int best = 2;
   double least = 1e30;
   for (int n = 2; n <= 4; ++n) {
-    const int m = (blocks + n - 1) / n, tiles = (blocks + m - 1) / m;
-    double groups = 0.0;
-    for (int j = 0; j < m; ++j) {
-      const double a = fmax(0.0, c0 + 16 * tiles * j - g.h);
-      const double b = fmin(g.Nv, fmin(c0 + 16 * tiles * (j + 1), c0 + side) + g.h);
-      groups += fmax(1.0, ceil((b - a) / 32.0 - 1e-9));
-    }
-    double cost = m * groups * pair[n];
-    if (tiles < n) cost *= np == 3 ? 0.9 : 0.75;
-    if (np == 3 && !adj_two_fit(g, np, n)) cost *= n < 4 ? 1.75 : 1.2;
+    const double cost = adj_cost(g, np, n, usual) + (np == 3 ? 0.7 : 2.0) * adj_cost(g, np, n, most);
     if (cost < least) {
       least = cost;
       best = n;
@@ -314,7 +324,7 @@ hipError_t launch_adj_np(const Geo<float>& g, int nb, const int4* box, const flo
   const bool turned = g.conv_du != g.box_du || g.conv_dv != g.box_dv;
   const double open = turned ? 0.9 : 0.95, wide = turned ? 1.4 : 2.0;
   const double ur = fmin(g.Nu, open * fu + wide * g.conv_du), uc = fmin(g.Nv, open * fv + wide * g.conv_dv);
-  const int n = adj_tiles(g, NP, fmax(ur, uc));
+  const int n = adj_tiles(g, NP, fmax(ur, uc), br > bc ? br : bc);
   const int pieces = ((br + 16 * n - 1) / (16 * n)) * ((bc + 16 * n - 1) / (16 * n));
   switch (n) {
     case 1: return launch_adj_cfg<NP, 1>(g, nb, pieces, box, z, in, out, s);
