@@ -249,9 +249,9 @@ int adj_waves(const Geo<float>& g, int np, int n) { return g.h <= 16 || (n == 4 
 
 // Estimated time of a rectangle of side `side` pixels in pieces of n x n tiles: column
 // groups over all pieces x time of a (group, tap row) pair, measured relative to pieces of
-// two: three 1.45 and four 2.8 (BF16: 1.2, 1.6), pieces that are a tile smaller than their
-// kernel 0.7 of that (BF16: three 0.8, four 0.9), and where FP32 windows leave one workgroup
-// to a compute unit 1.75 (pieces of four, which have few wavefronts anyway, 1.1).
+// two: three 1.45 and four 2.8 (BF16: 1.25, 1.55), pieces that are a tile smaller than their
+// kernel 0.7 of that (BF16 pieces of four: all of it), and where FP32 windows leave one
+// workgroup to a compute unit 1.75 (pieces of four, which have few wavefronts anyway, 1.1).
 double adj_cost(const Geo<float>& g, int np, int n, double side) {
   const int blocks = max(1, (int)ceil(side / 16.0)), m = (blocks + n - 1) / n, tiles = (blocks + m - 1) / m;
   const double c0 = 0.5 * (g.Nv - side);  // the rectangle's first column
@@ -261,9 +261,9 @@ double adj_cost(const Geo<float>& g, int np, int n, double side) {
     const double b = fmin(g.Nv, fmin(c0 + 16 * tiles * (j + 1), c0 + side) + g.h);
     groups += fmax(1.0, ceil((b - a) / 32.0 - 1e-9));
   }
-  const double pair[5] = {0.0, 0.0, 1.0, np == 3 ? 1.45 : 1.2, np == 3 ? 2.8 : 1.6};
+  const double pair[5] = {0.0, 0.0, 1.0, np == 3 ? 1.45 : 1.25, np == 3 ? 2.8 : 1.55};
   double cost = m * groups * pair[n];
-  if (tiles < n) cost *= np == 3 ? 0.7 : n < 4 ? 0.8 : 0.9;
+  if (tiles < n && (np == 3 || n < 4)) cost *= 0.7;
   if (np == 3 && !adj_two_fit(g, np, n)) cost *= n < 4 ? 1.75 : 1.1;
   return cost;
 }
@@ -272,7 +272,7 @@ double adj_cost(const Geo<float>& g, int np, int n, double side) {
 // `most` pixels: one piece up to three tiles; above, the least of both sides' times (a
 // rectangle at the limits may take a row of tiles more, and with it more pieces), weighed
 // as fits best 650 shapes of 13 to 61 taps and 7 to 97 pixels with and without corrections
-// and rotation, openings at the limits and up to a tenth inside: 1 : 0.7, BF16 1 : 2.  FP32,
+// and rotation, openings at the limits and up to a tenth inside: 1 : 0.7, BF16 1 : 1.  FP32,
 // 75 planes each:
 //   60 control points, n = 13, 57 x 57 pixels  0.136 ms in pieces of 2, 0.164 of 3, 0.156 of 4
 //   20, n = 13, 121 x 121                      0.168, 0.148, 0.191
@@ -285,7 +285,7 @@ int adj_tiles(const Geo<float>& g, int np, double usual, double most) {
   int best = 2;
   double least = 1e30;
   for (int n = 2; n <= 4; ++n) {
-    const double cost = adj_cost(g, np, n, usual) + (np == 3 ? 0.7 : 2.0) * adj_cost(g, np, n, most);
+    const double cost = adj_cost(g, np, n, usual) + (np == 3 ? 0.7 : 1.0) * adj_cost(g, np, n, most);
     if (cost < least) {
       least = cost;
       best = n;
